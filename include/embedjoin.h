@@ -130,7 +130,8 @@ typedef struct {
      * 1 persistent groups of pairs, 2 one pair per lane, 3 several lanes per
      * pair with several band words each (2 and 3: "verify_mode" 2), 4 grouped
      * by pattern ("verify_mode" 3), 5 the two-pass form with two or four
-     * band words per lane ("verify_wpl" 2 or 4). */
+     * band words per lane ("verify_wpl" 2 or 4), 6 the strip form (what
+     * "verify_mode" 0 runs with its other knobs at their defaults). */
     uint32_t verify_form;
     /* 1 when pairs and dist are device pointers (EJ_FLAG_DEVICE_OUT) */
     uint32_t on_device;
@@ -167,9 +168,15 @@ uint64_t ej_workspace_bytes(const ej_ctx *ctx);
  *                           runs; 0 in pair order
  *   "verify_blocks_per_cu"  workgroups per CU of the verification grid (the
  *                           lane form: at most, below the occupancy limit)
- *   "verify_mode"           0: two passes over fixed groups of pairs, one
- *                           band word per lane (the first C1 columns of all,
- *                           then the survivors);
+ *   "verify_mode"           0: the strip form (a pair's band in one lane's
+ *                           registers, or over up to 16 lanes when the pairs
+ *                           are few, narrowed after each strip of columns);
+ *                           with "verify_wpl", "verify_ring",
+ *                           "verify_pass1_cols", "verify_lds_budget",
+ *                           "verify_blocks_per_cu" or "verify_len_order" not
+ *                           at its default, two passes over fixed groups of
+ *                           pairs, one band word per lane (the first C1
+ *                           columns of all, then the survivors);
  *                           1: one persistent launch in which each pair's
  *                           lanes take the next pair from a device counter;
  *                           2: the lane form, persistent, with several band
@@ -359,7 +366,7 @@ ej_status ej_verify(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offse
  * whose workspace exceeds it are refused with EJ_ENOMEM before any
  * distance is written (a DNA set needs about 1.3 bytes per character plus 24
  * bytes per string; 25 letters about 4.2 bytes per character); use ej_verify
- * for those.  The two-pass verification form ("verify_mode" 0) runs as the
+ * for those.  Verification that keeps state per pair ("verify_mode" 0) runs as the
  * persistent form, which needs no per-pair state; no result changes.
  * Every call on one GPU uses that GPU's one array and leaves its contents
  * behind: calls that overlap on one GPU (from several host threads, or on

@@ -121,11 +121,9 @@ ej_status ej_calibrate(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_of
         // exact distances of the sample pairs: within K or not
         std::vector<int32_t> dist(count);
         if (count) {
-            RowMasks masks;
-            build_masks(ctx, pp.d_codes, d_offsets, pp.base, n, pp.total, pp.sigma, masks, "h");
             int32_t *d_dist = ws<int32_t>(ctx, "h_dist", count);
-            verify(ctx, pp.d_codes, d_offsets, pp.base, pp.sigma, pp.maxlen, masks, d_pairs, count,
-                   o->K, nullptr, d_dist);
+            verify(ctx, pp.sigma, verify_set(pp, d_offsets, "h"), nullptr, d_pairs, count, o->K,
+                   nullptr, d_dist);
             EJ_HIP(hipMemcpyAsync(dist.data(), d_dist, 4 * count, hipMemcpyDeviceToHost,
                                   ctx->stream));
             sync(ctx);

@@ -34,6 +34,7 @@ struct ej_index {
     uint32_t *d_len_s = nullptr;   // [T][n] lengths in sorted order
     uint32_t *d_ids = nullptr;     // [T][n] positions in sorted order
     RowMasks masks;                // match masks of the index strings (verification)
+    uint32_t *d_planes = nullptr;  // bit planes of their codes (verification)
     Rand rd;                       // random streams (owned copies)
     std::vector<void *> owned;
 };
@@ -354,13 +355,12 @@ ej_status ej_index_build(ej_ctx *ctx, const uint8_t *strings, const uint64_t *of
                                (const uint32_t *)pp.d_len, n, tot, ix->d_dk, ix->d_key_s,
                                ix->d_len_s);
         EJ_CHECK_LAUNCH();
-        // match masks of the index strings, kept for every query batch
-        {
-            uint32_t *mw = own_copy<uint32_t>(ix, nullptr, mask_words_bound(pp.total, n, pp.sigma));
-            uint64_t *mo = own_copy<uint64_t>(ix, nullptr, (uint64_t)n + 1);
-            build_masks(ctx, pp.d_codes, d_off, pp.base, n, pp.total, pp.sigma, ix->masks, "ixm",
-                        mw, mo);
-        }
+        // what verification needs of the index strings, kept for every query
+        // batch: the bit planes (the match masks of the other forms, five
+        // times their size, follow when a batch first asks for such a form)
+        ix->d_planes =
+            own_copy<uint32_t>(ix, nullptr, plane_words(pp.total) * plane_count(pp.sigma));
+        build_planes(ctx, pp.d_codes, pp.total, pp.sigma, ix->d_planes);
         // the owned offsets must be relative to the owned codes: base 0
         if (pp.base) {
             std::vector<uint64_t> h(n + 1);
@@ -449,8 +449,15 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         uint32_t *id = (uint32_t *)alloc(4 * totN);
         uint8_t *codes = (uint8_t *)alloc(charsN + 64);
         uint64_t *offs = (uint64_t *)alloc(8 * (nN + 1));
-        uint32_t *mw = (uint32_t *)alloc(4 * mask_words_bound(charsN, (uint32_t)nN, ix->sigma));
-        uint64_t *mo = (uint64_t *)alloc(8 * (nN + 1));
+        const bool masked = ix->masks.words != nullptr;  // a batch has asked for them
+        uint32_t *mw = nullptr;
+        uint64_t *mo = nullptr;
+        if (masked) {
+            mw = (uint32_t *)alloc(4 * mask_words_bound(charsN, (uint32_t)nN, ix->sigma));
+            mo = (uint64_t *)alloc(8 * (nN + 1));
+        }
+        uint32_t *planes =
+            (uint32_t *)alloc(4 * plane_words(charsN) * plane_count(ix->sigma));
         hipLaunchKernelGGL(k_merge_tables, dim3(grid_for(ctx, totN, 256)), dim3(256), 0,
                            ctx->stream, (const uint32_t *)ix->d_dk, (const uint64_t *)ix->d_key_s,
                            (const uint32_t *)ix->d_len_s, (const uint32_t *)ix->d_ids, ix->n,
@@ -471,11 +478,14 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
                            offs + ix->n);
         EJ_CHECK_LAUNCH();
         RowMasks masks;
-        build_masks(ctx, codes, offs, 0, (uint32_t)nN, charsN, ix->sigma, masks, "ixm", mw, mo);
+        if (masked)
+            build_masks(ctx, codes, offs, 0, (uint32_t)nN, charsN, ix->sigma, masks, "ixm", mw,
+                        mo);
+        build_planes(ctx, codes, charsN, ix->sigma, planes);
         sync(ctx);
         // swap in the grown arrays; release the replaced ones
         void *old[] = {ix->d_dk, ix->d_key_s, ix->d_len_s, ix->d_ids, ix->d_codes, ix->d_offsets,
-                       (void *)ix->masks.words, (void *)ix->masks.off};
+                       (void *)ix->masks.words, (void *)ix->masks.off, ix->d_planes};
         for (void *p : old) {
             auto it = std::find(ix->owned.begin(), ix->owned.end(), p);
             if (it != ix->owned.end()) ix->owned.erase(it);
@@ -490,6 +500,7 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         ix->d_codes = codes;
         ix->d_offsets = offs;
         ix->masks = masks;
+        ix->d_planes = planes;
         ix->n = (uint32_t)nN;
         ix->total = charsN;
         ix->maxlen = std::max(ix->maxlen, pq.maxlen);
@@ -617,10 +628,24 @@ ej_status ej_query_batch(ej_index *ix, const uint8_t *q, const uint64_t *q_offse
         int32_t *odist = nullptr;
         if (cnt) {
             int32_t *dist = ws<int32_t>(ctx, "q_dist", cnt);
-            RowMasks qmasks;
-            build_masks(ctx, pq.d_codes, dqo, 0, nq, pq.total, ix->sigma, qmasks, "qm");
-            verify(ctx, ix->d_codes, ix->d_offsets, 0, ix->sigma, ix->maxlen, ix->masks, pairs,
-                   cnt, 0, pk, dist, pq.d_codes, dqo, 0, pq.maxlen, &qmasks);
+            VerifySet sx;
+            sx.codes = ix->d_codes;
+            sx.off = ix->d_offsets;
+            sx.n = ix->n;
+            sx.total = ix->total;
+            sx.maxlen = ix->maxlen;
+            sx.tag = "ixm";
+            if (!strip_form(ctx) && !ix->masks.words) {
+                uint32_t *mw = own_copy<uint32_t>(
+                    ix, nullptr, mask_words_bound(ix->total, ix->n, ix->sigma));
+                uint64_t *mo = own_copy<uint64_t>(ix, nullptr, (uint64_t)ix->n + 1);
+                build_masks(ctx, ix->d_codes, ix->d_offsets, 0, ix->n, ix->total, ix->sigma,
+                            ix->masks, "ixm", mw, mo);
+            }
+            sx.masks = ix->masks;
+            sx.planes = ix->d_planes;
+            const VerifySet sq = verify_set(pq, dqo, "qm");
+            verify(ctx, ix->sigma, sx, &sq, pairs, cnt, 0, pk, dist);
             uint32_t *flags = ws<uint32_t>(ctx, "q_oflags", cnt);
             uint32_t *pos = ws<uint32_t>(ctx, "q_opos", cnt);
             uint64_t *d_no = ws<uint64_t>(ctx, "q_nout", 1);

@@ -353,15 +353,60 @@ inline uint64_t mask_words_bound(uint64_t total, uint32_t n, uint32_t sigma) {
     return (uint64_t)(sigma ? sigma : 1) * (total / 32 + n + 1);
 }
 
+// A string set of the verification: symbol codes, character offsets (the
+// first one is `base`), n strings of `total` characters, none longer than
+// maxlen.  Match masks and bit planes are built under `tag` when the form that
+// runs reads them, unless the caller keeps them (an index does).
+struct VerifySet {
+    const uint8_t *codes = nullptr;
+    const uint64_t *off = nullptr;
+    uint64_t base = 0;
+    uint32_t n = 0;
+    uint64_t total = 0;
+    uint32_t maxlen = 0;
+    const char *tag = "";
+    RowMasks masks;
+    const uint32_t *planes = nullptr;
+};
+
+inline VerifySet verify_set(const Prep &pp, const uint64_t *d_offsets, const char *tag) {
+    VerifySet s;
+    s.codes = pp.d_codes;
+    s.off = d_offsets;
+    s.base = pp.base;
+    s.n = pp.n;
+    s.total = pp.total;
+    s.maxlen = pp.maxlen;
+    s.tag = tag;
+    return s;
+}
+
 // Threshold edit distance of `count` pairs (codes a << 32 | b) over the
-// symbol codes of a string set (a) and a second set (b, or a again).
-void verify(ej_ctx *ctx, const uint8_t *d_codes, const uint64_t *d_offsets, uint64_t base,
-            uint32_t sigma, uint32_t maxlen, const RowMasks &masks, const uint64_t *d_pairs,
-            uint64_t count, uint32_t K, const uint32_t *d_Kq, int32_t *d_dist,
-            const uint8_t *d_codes_b = nullptr, const uint64_t *d_offsets_b = nullptr,
-            uint64_t base_b = 0, uint32_t maxlen_b = 0, const RowMasks *masks_b = nullptr,
-            unsigned long long *d_columns = nullptr, const uint32_t *d_order = nullptr,
-            const uint64_t *d_count = nullptr, uint32_t minlen = 0);
+// strings of set A (a) and set B (b; null: A).
+void verify(ej_ctx *ctx, uint32_t sigma, VerifySet A, const VerifySet *B,
+            const uint64_t *d_pairs, uint64_t count, uint32_t K, const uint32_t *d_Kq,
+            int32_t *d_dist, unsigned long long *d_columns = nullptr,
+            const uint32_t *d_order = nullptr, const uint64_t *d_count = nullptr,
+            uint32_t minlen = 0);
+
+// Bit planes of a code array: plane_count(sigma) words per 32 letters.
+uint32_t plane_count(uint32_t sigma);
+inline uint64_t plane_words(uint64_t total) { return total / 32 + 2; }
+void build_planes(ej_ctx *ctx, const uint8_t *d_codes, uint64_t total, uint32_t sigma,
+                  uint32_t *d_planes);
+
+// Strip form of the verification (ej_strip.hip), and whether the context's
+// knobs select it.
+bool strip_form(const ej_ctx *ctx);
+struct StripSet {
+    const uint32_t *planes;
+    const uint64_t *off;
+    uint64_t base, total;
+};
+void verify_strips(ej_ctx *ctx, uint32_t sigma, const StripSet &A, const StripSet &B,
+                   const uint64_t *d_pairs, uint64_t count, uint32_t K, const uint32_t *d_Kq,
+                   uint32_t Kmax, uint32_t mtext, int32_t *d_dist,
+                   unsigned long long *d_columns, const uint64_t *d_count);
 
 uint32_t verify_lanes_for(uint32_t K);  // lanes per pair, 0 if unsupported
 

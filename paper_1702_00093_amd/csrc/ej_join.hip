@@ -269,11 +269,8 @@ void finish_join(ej_ctx *ctx, const Prep &pp, const uint64_t *d_offsets, const e
         ctx->timers.nkv = 0;
         ctx->timers.more = 0;
         ctx->graph_on = (p.flags & EJ_FLAG_GRAPH) != 0 && ctx->tune.verify_mode >= 1;
-        RowMasks masks;
-        if (cnt)
-            build_masks(ctx, pp.d_codes, d_offsets, pp.base, n, pp.total, pp.sigma, masks, "j");
-        verify(ctx, pp.d_codes, d_offsets, pp.base, pp.sigma, pp.maxlen, masks, pairs, cnt, p.K,
-               nullptr, dist, nullptr, nullptr, 0, 0, nullptr, d_cols, order, nullptr, pp.minlen);
+        verify(ctx, pp.sigma, verify_set(pp, d_offsets, "j"), nullptr, pairs, cnt, p.K, nullptr,
+               dist, d_cols, order, nullptr, pp.minlen);
     }
     tm.mark();  // 5
     uint64_t nout = 0;
@@ -466,8 +463,10 @@ bool join_graph(ej_ctx *ctx, const Prep &pp, const Rand &rd, const uint64_t *d_o
     const uint32_t T = p.r * p.z;
     const uint64_t raw_cap = caps.raw_cap, cnt_cap = caps.cnt_cap;
     // the multiplicity order schedules the two-pass, persistent and lane
-    // forms (the grouped form orders by pattern itself)
-    const bool want_order = ctx->tune.verify_mode <= 2 && ctx->tune.verify_order == 1;
+    // forms (the grouped form orders by pattern itself, the strip form by
+    // what is left of the pairs' bands)
+    const bool want_order =
+        ctx->tune.verify_mode <= 2 && ctx->tune.verify_order == 1 && !strip_form(ctx);
     uint64_t *cnt_dev = ws<uint64_t>(ctx, "jg_counts", 4);
     uint64_t *cnt_out = ws<uint64_t>(ctx, "jg_counts_out", 4);
     // results: pairs [2 * cnt_cap] u32, then distances [cnt_cap] (looked up
@@ -488,11 +487,8 @@ bool join_graph(ej_ctx *ctx, const Prep &pp, const Rand &rd, const uint64_t *d_o
                        caps.sort_dedup || ctx->tune.dedup_sort != 0, cnt_dev, &pairs, &order,
                        "j");
         int32_t *dist = ws<int32_t>(ctx, "j_dist", cnt_cap);
-        RowMasks masks;
-        build_masks(ctx, pp.d_codes, d_offsets, pp.base, n, pp.total, pp.sigma, masks, "j");
-        verify(ctx, pp.d_codes, d_offsets, pp.base, pp.sigma, pp.maxlen, masks, pairs, cnt_cap,
-               p.K, nullptr, dist, nullptr, nullptr, 0, 0, nullptr, nullptr, order, cnt_dev + 1,
-               pp.minlen);
+        verify(ctx, pp.sigma, verify_set(pp, d_offsets, "j"), nullptr, pairs, cnt_cap, p.K,
+               nullptr, dist, nullptr, order, cnt_dev + 1, pp.minlen);
         uint32_t *flags = ws<uint32_t>(ctx, "j_oflags", cnt_cap);
         uint32_t *pos = ws<uint32_t>(ctx, "j_opos", cnt_cap);
         hipLaunchKernelGGL(k_out_flags, dim3(grid_for(ctx, cnt_cap, 256)), dim3(256), 0,
@@ -639,8 +635,10 @@ void join_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets,
     uint64_t raw = 0;
     uint32_t *order = nullptr;
     // the multiplicity order schedules the two-pass, persistent and lane
-    // forms (the grouped form orders by pattern itself)
-    const bool want_order = ctx->tune.verify_mode <= 2 && ctx->tune.verify_order == 1;
+    // forms (the grouped form orders by pattern itself, the strip form by
+    // what is left of the pairs' bands)
+    const bool want_order =
+        ctx->tune.verify_mode <= 2 && ctx->tune.verify_order == 1 && !strip_form(ctx);
     uint64_t cnt = candidates(ctx, keys, bk, pp.d_len, p.K, &pairs, &raw, "j",
                               want_order && !p.exact_len ? &order : nullptr);
     const uint64_t *cp = pairs;
@@ -871,11 +869,8 @@ void verify_entry(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets
     Prep pp;
     prepare(ctx, d_chars, d_offsets, n, 0, pp, "v", nullptr, 0, 0, false);
     check_pairs(ctx, d_pairs, count, n, n);
-    RowMasks masks;
-    if (count)
-        build_masks(ctx, pp.d_codes, d_offsets, pp.base, n, pp.total, pp.sigma, masks, "v");
-    verify(ctx, pp.d_codes, d_offsets, pp.base, pp.sigma, pp.maxlen, masks, d_pairs, count, K,
-           d_Kq, d_dist, nullptr, nullptr, 0, 0, nullptr, nullptr, nullptr, nullptr, pp.minlen);
+    verify(ctx, pp.sigma, verify_set(pp, d_offsets, "v"), nullptr, d_pairs, count, K, d_Kq, d_dist,
+           nullptr, nullptr, nullptr, pp.minlen);
     sync(ctx);
 }
 

@@ -40,6 +40,7 @@
 
 #include <algorithm>
 
+#include "ej_bits.h"
 #include "ej_internal.h"
 
 namespace ej {
@@ -65,20 +66,6 @@ __device__ inline uint32_t lanes_of(uint32_t nl) {
     return MODE == LANES_ONE ? 1u : MODE == LANES_ROW ? 16u : MODE == LANES_WAVE ? 64u : nl;
 }
 
-// s = a + b; the carry-out of every lane lands in one wave-wide mask.
-__device__ inline uint32_t add_carry_mask(uint32_t a, uint32_t b, uint64_t &carry) {
-    uint32_t s;
-    asm("v_add_co_u32 %0, %1, %2, %3" : "=v"(s), "=s"(carry) : "v"(a), "v"(b));
-    return s;
-}
-
-// s = a + b + (bit `lane` of cin); carry-outs of every lane in cout.
-__device__ inline uint32_t add_carry_chain(uint32_t a, uint32_t b, uint64_t cin, uint64_t &cout) {
-    uint32_t s;
-    asm("v_addc_co_u32 %0, %1, %2, %3, %4" : "=v"(s), "=s"(cout) : "v"(a), "v"(b), "s"(cin));
-    return s;
-}
-
 // s = a + (bit `lane` of the wave-wide mask cin): one add with the carry-in
 // taken straight from the scalar mask.
 __device__ inline uint32_t add_carry_in(uint32_t a, uint64_t cin) {
@@ -102,13 +89,6 @@ __device__ inline void add_columns(unsigned long long *columns, unsigned long lo
     if (!columns) return;
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
     if ((threadIdx.x & 63u) == 0 && v) atomicAdd(columns, v);
-}
-
-// popcount(x) + acc in one v_bcnt.
-__device__ inline uint32_t popc_acc(uint32_t x, uint32_t acc) {
-    uint32_t r;
-    asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(r) : "v"(x), "v"(acc));
-    return r;
 }
 
 template <int MODE>
@@ -1857,6 +1837,17 @@ uint32_t verify_lanes_for(uint32_t K) {
     return nl <= 64 ? (uint32_t)nl : 0u;
 }
 
+bool strip_form(const ej_ctx *ctx) {
+    // a knob of the two-pass form that is not at its default asks for that
+    // form; a caller's fixed scratch (arena) holds no survivors' state
+    const Tuning &t = ctx->tune, dflt;
+    return t.verify_mode == 0 && t.verify_wpl == dflt.verify_wpl &&
+           t.verify_ring == dflt.verify_ring && t.verify_pass1_cols == dflt.verify_pass1_cols &&
+           t.verify_lds_budget == dflt.verify_lds_budget &&
+           t.verify_blocks_per_cu == dflt.verify_blocks_per_cu &&
+           t.verify_len_order == dflt.verify_len_order && !ctx->arena.base;
+}
+
 void build_masks(ej_ctx *ctx, const uint8_t *d_codes, const uint64_t *d_offsets, uint64_t base,
                  uint32_t n, uint64_t total, uint32_t sigma, RowMasks &rm, const char *tag,
                  uint32_t *own_words, uint64_t *own_off) {
@@ -1888,12 +1879,10 @@ void build_masks(ej_ctx *ctx, const uint8_t *d_codes, const uint64_t *d_offsets,
     EJ_CHECK_LAUNCH();
 }
 
-void verify(ej_ctx *ctx, const uint8_t *d_codes, const uint64_t *d_offsets, uint64_t base,
-            uint32_t sigma, uint32_t maxlen, const RowMasks &masks, const uint64_t *d_pairs,
-            uint64_t count, uint32_t K, const uint32_t *d_Kq, int32_t *d_dist,
-            const uint8_t *d_codes_b, const uint64_t *d_offsets_b, uint64_t base_b,
-            uint32_t maxlen_b, const RowMasks *masks_b, unsigned long long *d_columns,
-            const uint32_t *d_order, const uint64_t *d_count, uint32_t minlen) {
+void verify(ej_ctx *ctx, uint32_t sigma, VerifySet SA, const VerifySet *setB,
+            const uint64_t *d_pairs, uint64_t count, uint32_t K, const uint32_t *d_Kq,
+            int32_t *d_dist, unsigned long long *d_columns, const uint32_t *d_order,
+            const uint64_t *d_count, uint32_t minlen) {
     if (count == 0) return;
     if (count >= 0xFFFFFFFFull) fail(EJ_EUNSUPPORTED, "more than 2^32 pairs in one verification");
     uint32_t Kmax = K;
@@ -1909,16 +1898,50 @@ void verify(ej_ctx *ctx, const uint8_t *d_codes, const uint64_t *d_offsets, uint
     if (NL == 0)
         fail(EJ_EUNSUPPORTED,
              "threshold " + std::to_string(Kmax) + " exceeds 2046 (band > 2048 bits)");
-    const bool self_set = d_codes_b == nullptr;  // the pairs are of one string set
-    if (!d_codes_b) {
-        d_codes_b = d_codes;
-        d_offsets_b = d_offsets;
-        base_b = base;
-        maxlen_b = maxlen;
-        masks_b = &masks;
+    const bool self_set = setB == nullptr;  // the pairs are of one string set
+    VerifySet SB = self_set ? SA : *setB;
+    const uint32_t maxlen = SA.maxlen, maxlen_b = SB.maxlen;
+    Timers &tk = ctx->timers;
+    auto kmark = [&]() {
+        if (tk.on && tk.nkv < 4) EJ_HIP(hipEventRecord(tk.kv[tk.nkv++], ctx->stream));
+    };
+    // (word positions in the planes are 32-bit)
+    if (strip_form(ctx) && std::max(plane_words(SA.total), plane_words(SB.total)) < 0x7FFFFF00ull) {
+        ctx->last_verify_form = 6;
+        auto planes = [&](VerifySet &S) {
+            if (S.planes) return;
+            uint32_t *p = ws<uint32_t>(ctx, std::string(S.tag) + "_planes",
+                                       plane_words(S.total) * plane_count(sigma));
+            build_planes(ctx, S.codes, S.total, sigma, p);
+            S.planes = p;
+        };
+        planes(SA);
+        if (self_set)
+            SB = SA;
+        else
+            planes(SB);
+        kmark();
+        verify_strips(ctx, sigma, StripSet{SA.planes, SA.off, SA.base, SA.total},
+                      StripSet{SB.planes, SB.off, SB.base, SB.total}, d_pairs, count, K, d_Kq,
+                      Kmax, std::min(maxlen, maxlen_b), d_dist, d_columns, d_count);
+        kmark();
+        return;
     }
-    const StrSet A{d_codes, d_offsets, base, masks.words, masks.off};
-    const StrSet B{d_codes_b, d_offsets_b, base_b, masks_b->words, masks_b->off};
+    auto need_masks = [&](VerifySet &S) {
+        if (!S.masks.words)
+            build_masks(ctx, S.codes, S.off, S.base, S.n, S.total, sigma, S.masks, S.tag);
+    };
+    need_masks(SA);
+    if (self_set)
+        SB = SA;
+    else
+        need_masks(SB);
+    const RowMasks &masks = SA.masks;
+    const uint8_t *d_codes = SA.codes, *d_codes_b = SB.codes;
+    const uint64_t *d_offsets = SA.off, *d_offsets_b = SB.off;
+    const uint64_t base = SA.base, base_b = SB.base;
+    const StrSet A{d_codes, d_offsets, base, SA.masks.words, SA.masks.off};
+    const StrSet B{d_codes_b, d_offsets_b, base_b, SB.masks.words, SB.masks.off};
     const uint32_t sig = sigma ? sigma : 1;
     const uint32_t W = 32 * NL;
     const uint32_t mtext = std::min(maxlen, maxlen_b);
@@ -1943,10 +1966,6 @@ void verify(ej_ctx *ctx, const uint8_t *d_codes, const uint64_t *d_offsets, uint
     tpw = std::min(tpw, budget / tile_bytes);
     const size_t lds = (size_t)tpw * tile_bytes;
     const int mode = NL == 1 ? LANES_ONE : NL == 16 ? LANES_ROW : NL == 64 ? LANES_WAVE : LANES_ANY;
-    Timers &tk = ctx->timers;
-    auto kmark = [&]() {
-        if (tk.on && tk.nkv < 4) EJ_HIP(hipEventRecord(tk.kv[tk.nkv++], ctx->stream));
-    };
     // grouped by pattern: the candidates' patterns share LDS rows per chunk
     if (ctx->tune.verify_mode == 3 && self_set && NL <= LANE_MAX_WORDS && masks.n > 0) {
         const uint32_t lead = (Kmax / 2 + 1 + 31) / 32;
