@@ -258,6 +258,19 @@ __global__ void k_draw_lsh(uint64_t seed, uint32_t r, uint32_t z, uint32_t m, ui
     }
 }
 
+// Coordinates of the tables of groups with walk lengths of their own: row
+// g * r + l, as k_draw_lsh draws them for walks of L[g] steps.
+__global__ void k_draw_group_pos(uint64_t seed, uint32_t r, uint32_t z, uint32_t m,
+                                 const uint32_t *__restrict__ L, uint32_t ng,
+                                 uint32_t *__restrict__ pos) {
+    const uint32_t per = r * z * m, tot = ng * per;
+    for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < tot; e += gridDim.x * blockDim.x) {
+        const uint32_t g = e / per, x = e - g * per;
+        const uint64_t kp = stream_key(seed, TAG_POS, x / m);
+        pos[e] = (uint32_t)__umul64hi(rng_word(kp, x % m), (uint64_t)L[g]);
+    }
+}
+
 // Per seed: the z*m samples (step, slot j*m+k) in ascending (step, slot)
 // order, and J = last sampled step + 1.  Rank by counting (S is small).
 __global__ void k_sample_sort(const uint32_t *__restrict__ pos, uint32_t S,
@@ -293,8 +306,6 @@ __global__ void k_sample_sort(const uint32_t *__restrict__ pos, uint32_t S,
 // itself never looks at the sample list.  REC = false: the walk stores each
 // sampled symbol as it passes the sample's step (the positions sorted, one
 // scalar read per sample).
-constexpr uint32_t EMBED_REC_STEPS = 256;
-
 template <int BW, bool RSTEP, bool REC>
 __global__ void __launch_bounds__(64)
     k_embed(const uint32_t *__restrict__ packed, const uint64_t *__restrict__ offsets,
@@ -305,7 +316,8 @@ __global__ void __launch_bounds__(64)
             const uint32_t *__restrict__ pos, uint32_t Lb, const uint64_t *__restrict__ v,
             uint32_t r, uint32_t z, uint32_t m, uint32_t sigma, uint32_t slot_words,
             uint64_t *__restrict__ keys, uint8_t *__restrict__ sig_out,
-            uint32_t *__restrict__ dk_out, uint32_t *__restrict__ ids_out, uint32_t dk_shift) {
+            uint32_t *__restrict__ dk_out, uint32_t *__restrict__ ids_out, uint32_t dk_shift,
+            const uint4 *__restrict__ chunks) {
     constexpr uint32_t CPD = 32 / BW;
     constexpr uint32_t LOGBW = BW == 2 ? 1 : (BW == 4 ? 2 : 3);
     constexpr uint32_t LOGCPD = 5 - LOGBW;
@@ -318,14 +330,20 @@ __global__ void __launch_bounds__(64)
     const uint32_t stride = slot_words + 1;
     const uint32_t lane = threadIdx.x;
     const uint32_t chunk = blockIdx.x / r, l = blockIdx.x % r;
-    const uint32_t rank = chunk * 64 + lane;
-    const bool valid = rank < n;
+    uint32_t rank = chunk * 64 + lane, row = l;
+    bool valid = rank < n;
+    if (chunks) {
+        const uint4 c = chunks[chunk];
+        rank = c.x + lane;
+        valid = lane < c.y;
+        row = c.z * r + l;
+    }
     const uint32_t id = valid ? perm[rank] : 0;
     const uint32_t slen = valid ? len[id] : 0;
     const uint64_t s0 = valid ? offsets[id] - base : 0;
-    const uint32_t J = Jarr[l];
-    const uint32_t *sp = spos + (size_t)l * S;
-    const uint32_t *ss = sslot + (size_t)l * S;
+    const uint32_t J = Jarr[row];
+    const uint32_t *sp = spos + (size_t)row * S;
+    const uint32_t *ss = sslot + (size_t)row * S;
     const uint32_t *Rs = Rstep + (size_t)l * Lpad;
     const uint32_t *Rw = Rwords + (size_t)l * nw;
     uint32_t *myslot = slots + lane * stride;
@@ -341,6 +359,12 @@ __global__ void __launch_bounds__(64)
         // ---- stage the next window of every string of the wave into LDS
         __syncthreads();
         const bool live = i < slen;
+        if (!REC && __builtin_amdgcn_ballot_w64(live) == 0) {
+            // every string is used up: bottom from here on (a walk of three
+            // times the length is, after two thirds of its steps)
+            for (; k < S; k++) sig[ss[k] * 64 + lane] = (uint8_t)sigma;
+            break;
+        }
         uint64_t gq = (s0 + i) >> LOGCPD;
         uint32_t p0 = (uint32_t)((s0 + i) & (CPD - 1));
         uint32_t nd = 0;
@@ -437,7 +461,7 @@ __global__ void __launch_bounds__(64)
     for (uint32_t t = 0; t < z; t++) {
         const uint64_t *vt = v + ((size_t)l * z + t) * m;
         uint32_t s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-        const uint32_t *pt = pos + (size_t)l * S + t * m;
+        const uint32_t *pt = pos + (size_t)row * S + t * m;
         for (uint32_t kk = 0; kk < m; kk++) {
             const uint32_t u =
                 (uint32_t)(REC ? rec[pt[kk]] : sig[(t * m + kk) * 64 + lane]) + 1u;
@@ -453,10 +477,11 @@ __global__ void __launch_bounds__(64)
         uint64_t res = (uint64_t)(x & P61) + (uint64_t)(x >> 61);
         res = (res & P61) + (res >> 61);
         if (res >= P61) res -= P61;
-        keys[((size_t)l * z + t) * n + id] = res;
+        const uint32_t at = chunks ? rank : id;
+        keys[((size_t)l * z + t) * n + at] = res;
         if (dk_out) {
             dk_out[((size_t)l * z + t) * n + rank] = (uint32_t)(res >> dk_shift);
-            ids_out[((size_t)l * z + t) * n + rank] = id;
+            ids_out[((size_t)l * z + t) * n + rank] = at;
         }
         if (sig_out) {
             uint8_t *dst = sig_out + (((size_t)id * r + l) * z + t) * m;
@@ -620,6 +645,7 @@ void prepare(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets, uin
         uint32_t *iota = ws<uint32_t>(ctx, t + "_iota", n);
         uint32_t *lk2 = ws<uint32_t>(ctx, t + "_lenkey2", n);
         pp.d_perm = ws<uint32_t>(ctx, t + "_perm", n);
+        pp.d_perm_len = lk2;
         EJ_HIP(hipMemcpyAsync(lk, pp.d_len, n * sizeof(uint32_t), hipMemcpyDeviceToDevice,
                               ctx->stream));
         hipLaunchKernelGGL(k_iota, dim3(grid_for(ctx, n, 256)), dim3(256), 0, ctx->stream, iota, n);
@@ -685,8 +711,25 @@ void draw_randomness(ej_ctx *ctx, const ej_params &p, uint32_t L, uint32_t sigma
     rd.Jmax = L;
 }
 
+void draw_group_samples(ej_ctx *ctx, const ej_params &p, const uint32_t *d_L, uint32_t ng,
+                        Rand &rd, const char *tag) {
+    const std::string t(tag);
+    const uint64_t tot = (uint64_t)ng * rd.r * rd.S;
+    rd.d_pos = ws<uint32_t>(ctx, t + "_gpos", tot);
+    rd.d_spos = ws<uint32_t>(ctx, t + "_gspos", tot);
+    rd.d_sslot = ws<uint32_t>(ctx, t + "_gsslot", tot);
+    rd.d_J = ws<uint32_t>(ctx, t + "_gJ", (uint64_t)ng * rd.r);
+    hipLaunchKernelGGL(k_draw_group_pos, dim3(grid_for(ctx, tot, 256)), dim3(256), 0, ctx->stream,
+                       p.seed, p.r, p.z, p.m, d_L, ng, rd.d_pos);
+    EJ_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_sample_sort, dim3(ng * rd.r), dim3(256), 0, ctx->stream,
+                       (const uint32_t *)rd.d_pos, rd.S, rd.d_spos, rd.d_sslot, rd.d_J);
+    EJ_CHECK_LAUNCH();
+}
+
 void embed_keys(ej_ctx *ctx, const Prep &pp, const Rand &rd, uint64_t *d_keys, uint8_t *d_sig,
-                uint32_t *d_dk, uint32_t *d_rank_ids, uint32_t dk_shift) {
+                uint32_t *d_dk, uint32_t *d_rank_ids, uint32_t dk_shift, const uint4 *d_chunks,
+                uint32_t nchunks) {
     if (pp.n == 0) return;
     const uint32_t S = rd.S;
     // short walks keep their whole record (Lb bytes per lane, Lb / 4 odd so
@@ -711,7 +754,7 @@ void embed_keys(ej_ctx *ctx, const Prep &pp, const Rand &rd, uint64_t *d_keys, u
     uint32_t need = (std::min(pp.maxlen, pp.L) + cpd - 1) / cpd + 4;
     if (slot_words > need) slot_words = std::max(need, 8u);
     size_t lds = sigbytes + (size_t)64 * (slot_words + 1) * 4;
-    dim3 grid(rd.r * ceil_div(pp.n, 64)), block(64);
+    dim3 grid(rd.r * (d_chunks ? nchunks : ceil_div(pp.n, 64))), block(64);
     const bool rstep = rd.sigma <= 32;
     auto launch = [&](auto kern) {
         if (lds > 65536)
@@ -724,7 +767,7 @@ void embed_keys(ej_ctx *ctx, const Prep &pp, const Rand &rd, uint64_t *d_keys, u
                            (const uint32_t *)rd.d_sslot, (const uint32_t *)rd.d_J,
                            (const uint32_t *)rd.d_pos, Lb, (const uint64_t *)rd.d_v, rd.r, rd.z,
                            rd.m, rd.sigma, slot_words, d_keys,
-                           d_sig, d_dk, d_rank_ids, dk_shift);
+                           d_sig, d_dk, d_rank_ids, dk_shift, d_chunks);
         EJ_CHECK_LAUNCH();
     };
     if (rec) {

@@ -236,6 +236,7 @@ struct Prep {
     uint8_t *d_codes = nullptr;     // [total] symbol codes, same layout as chars (base-relative)
     uint32_t *d_packed = nullptr;   // packed codes, bw bits each, base-relative
     uint32_t *d_perm = nullptr;     // [n] positions in (length, position) order
+    uint32_t *d_perm_len = nullptr; // [n] lengths in that order
 };
 
 struct Rand {
@@ -264,8 +265,19 @@ void draw_randomness(ej_ctx *ctx, const ej_params &p, uint32_t L, uint32_t sigma
 // With d_dk (and d_rank_ids), also the bucketing sort's input: for table t
 // and length rank k, d_dk[t*n + k] = key >> dk_shift of the string of rank k
 // and d_rank_ids[t*n + k] = that string's index.
+// With d_chunks, the entries of several groups that share the alphabet and
+// the pi bits and have sample positions of their own (draw_group_samples):
+// nchunks chunks of up to 64 entries of one group each (x = first entry, y =
+// entries, z = group).  pp.n is then the number of entries, pp.d_perm maps an
+// entry to its string, and keys and d_rank_ids are by entry.
 void embed_keys(ej_ctx *ctx, const Prep &pp, const Rand &rd, uint64_t *d_keys, uint8_t *d_sig,
-                uint32_t *d_dk = nullptr, uint32_t *d_rank_ids = nullptr, uint32_t dk_shift = 0);
+                uint32_t *d_dk = nullptr, uint32_t *d_rank_ids = nullptr, uint32_t dk_shift = 0,
+                const uint4 *d_chunks = nullptr, uint32_t nchunks = 0);
+// Sample positions of ng groups with walk lengths d_L, in place of rd's own
+// (row g * r + l: those draw_randomness draws for walks of d_L[g] steps).
+void draw_group_samples(ej_ctx *ctx, const ej_params &p, const uint32_t *d_L, uint32_t ng,
+                        Rand &rd, const char *tag);
+constexpr uint32_t EMBED_REC_STEPS = 256;  // walks up to this long keep their whole record
 
 // Distortion diagnostic: d_ham[e * r + l] = Hamming distance between the
 // first L symbols of the embeddings of pair e's strings under seed l (the

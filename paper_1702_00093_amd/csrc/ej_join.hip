@@ -2,6 +2,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <chrono>
 #include <vector>
 
@@ -136,13 +137,79 @@ __global__ void k_gather_strings(const uint8_t *__restrict__ chars,
     }
 }
 
-// A group's candidate codes (local positions) to positions in the whole set.
+// Grouping: the entry e of group g (gstart[g] <= e < gstart[g + 1]) is the
+// string at place glo[g] + e - gstart[g] of the length order.
+__device__ inline uint32_t group_of(uint32_t e, const uint32_t *__restrict__ gstart, uint32_t ng) {
+    uint32_t lo = 0, hi = ng;
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (gstart[mid] <= e) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+// The letters of every group (bits of the whole set's codes, 8 words per
+// group).  A wave reads the strings of a chunk of a group (see embed_keys) one
+// after the other, 256 letters at a time, until every letter has shown: on an
+// ordinary set that is the first string's first letters.
+__global__ void __launch_bounds__(64)
+    k_group_alphabet(const uint8_t *__restrict__ codes, const uint64_t *__restrict__ offsets,
+                     uint64_t base, const uint32_t *__restrict__ perm,
+                     const uint32_t *__restrict__ gstart, const uint32_t *__restrict__ glo,
+                     const uint4 *__restrict__ chunks, uint32_t sigma,
+                     uint32_t *__restrict__ gmask) {
+    const uint32_t lane = threadIdx.x;
+    const uint4 chunk = chunks[blockIdx.x];
+    const uint32_t g = chunk.z;
+    const uint32_t *p = perm + glo[g] + (chunk.x - gstart[g]);
+    for (uint32_t w = 0; w * 32 < sigma; w++) {
+        const uint32_t full = sigma - w * 32 >= 32 ? ~0u : (1u << (sigma - w * 32)) - 1u;
+        uint32_t seen = 0;
+        for (uint32_t e = 0; e < chunk.y && seen != full; e++) {
+            const uint32_t id = p[e];
+            const uint64_t s0 = offsets[id] - base, len = offsets[id + 1] - offsets[id];
+            for (uint64_t c = 0; c < len && seen != full; c += 256) {
+                uint32_t bit = 0;
+#pragma unroll
+                for (uint32_t u = 0; u < 256; u += 64)
+                    if (c + u + lane < len) {
+                        const uint32_t x = codes[s0 + c + u + lane];
+                        bit |= (x >> 5) == w ? 1u << (x & 31u) : 0u;
+                    }
+                for (int o = 32; o > 0; o >>= 1) bit |= (uint32_t)__shfl_xor((int)bit, o, 64);
+                seen |= bit;
+            }
+        }
+        if (lane == 0 && seen) atomicOr(&gmask[g * 8 + w], seen);
+    }
+}
+
+// The entries' strings, and lengths that set groups further apart than the
+// length filter reaches (span = longest string + K + 1): one candidate stage
+// then serves all groups, and pairs none of two groups.
+__global__ void k_group_entries(const uint32_t *__restrict__ perm,
+                                const uint32_t *__restrict__ perm_len,
+                                const uint32_t *__restrict__ gstart,
+                                const uint32_t *__restrict__ glo, uint32_t ng, uint32_t entries,
+                                uint32_t span, uint32_t *__restrict__ ids,
+                                uint32_t *__restrict__ len) {
+    for (uint32_t e = blockIdx.x * blockDim.x + threadIdx.x; e < entries;
+         e += gridDim.x * blockDim.x) {
+        const uint32_t g = group_of(e, gstart, ng);
+        const uint32_t k = glo[g] + e - gstart[g];
+        ids[e] = perm[k];
+        len[e] = perm_len[k] + g * span;
+    }
+}
+
+// Candidate codes of entries (local positions) to positions in the whole set.
 __global__ void k_map_pairs(const uint64_t *__restrict__ pairs, uint64_t cnt,
                             const uint32_t *__restrict__ ids, uint64_t *__restrict__ out) {
     for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e < cnt;
          e += (uint64_t)gridDim.x * blockDim.x) {
         const uint64_t c = pairs[e];
-        out[e] = ((uint64_t)ids[c >> 32] << 32) | ids[(uint32_t)c];
+        const uint32_t a = ids[c >> 32], b = ids[(uint32_t)c];
+        out[e] = ((uint64_t)min(a, b) << 32) | max(a, b);
     }
 }
 
@@ -748,13 +815,43 @@ void check_pairs(ej_ctx *ctx, const uint64_t *d_pairs, uint64_t count, uint32_t 
     if (bad) fail(EJ_EINVAL, "a pair refers to a position >= n");
 }
 
-// Length groups of the grouping alternative to truncation (Section 4.1):
-// group g holds the strings of length in (gK, (g+2)K] (group 0 also the
-// empty ones; one group per length when K = 0), g < max(1, ceil(N/K) - 1).
-inline bool in_group(uint64_t len, uint64_t g, uint32_t K) {
-    if (K == 0) return len == g;
-    if (g == 0 && len == 0) return true;
-    return len > g * K && len <= (g + 2) * K;
+// A length group of the grouping alternative to truncation (Section 4.1):
+// group g holds the strings of length in (gK, (g+2)K] (group 0 also the empty
+// ones; one group per length when K = 0), g < max(1, ceil(N/K) - 1): the k
+// strings from place lo of the length order.
+struct LenGroup {
+    uint32_t lo, k;
+    uint32_t L;      // walk length
+    bool own;        // a front end of its own (see join_grouped_device)
+};
+
+std::vector<LenGroup> length_groups(const std::vector<uint32_t> &slen, const ej_params &p) {
+    const uint64_t n = slen.size(), K = p.K, N = n ? slen[n - 1] : 0;
+    std::vector<LenGroup> out;
+    auto add = [&](uint64_t lo, uint64_t hi) {
+        if (hi - lo < 2) return;
+        const uint64_t Ng = slen[hi - 1];
+        uint64_t L = p.L ? p.L : std::max<uint64_t>(1, 3 * Ng);
+        if (L > 0x7FFFFFFFull) fail(EJ_EUNSUPPORTED, "group walk length too large");
+        L = std::max<uint64_t>(1, std::min(L, 3 * Ng));
+        out.push_back(LenGroup{(uint32_t)lo, (uint32_t)(hi - lo), (uint32_t)L, false});
+    };
+    if (K == 0) {
+        for (uint64_t lo = 0, hi; lo < n; lo = hi) {
+            for (hi = lo; hi < n && slen[hi] == slen[lo]; hi++) {
+            }
+            add(lo, hi);
+        }
+        return out;
+    }
+    const uint64_t G = std::max<uint64_t>(1, (N + K - 1) / K - 1);
+    uint64_t lo = 0, hi = 0;
+    for (uint64_t g = 0; g < G; g++) {
+        while (g && lo < n && slen[lo] <= g * K) lo++;
+        while (hi < n && slen[hi] <= (g + 2) * K) hi++;
+        add(lo, hi);
+    }
+    return out;
 }
 
 // EmbedJoin with grouping instead of truncation: the front end (A0-A4) runs
@@ -762,6 +859,15 @@ inline bool in_group(uint64_t len, uint64_t g, uint32_t K) {
 // L = 3 x its longest string, or the caller's L), the groups' candidates are
 // mapped to positions in the whole set and de-duplicated, and the union is
 // verified once (a pair found by two groups is verified once, not twice).
+//
+// A group whose strings use the whole set's alphabet draws the same pi bits
+// as its neighbours (the streams do not depend on the walk length; the sample
+// positions do), so such groups go through one front end together, in
+// batches: a group's walks alone are some hundred waves that each take 30 ns
+// a step, and group after group left the chip idle (8,000 strings of 500 to
+// 12,000 letters, 29 groups: 31 ms of walks, 0.8 ms together).  Groups that lack
+// a letter, and those that may be meant by explicit randomness, keep a front
+// end of their own.
 void join_grouped_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets,
                          uint32_t n, const ej_params &p, ej_result *out) {
     check_params(p, n);
@@ -771,13 +877,13 @@ void join_grouped_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_
     Prep pp;
     prepare(ctx, d_chars, d_offsets, n, 0, pp, "j");
     out->sigma = pp.sigma;
-    std::vector<uint32_t> len(n);
+    std::vector<uint32_t> slen(n);
     if (n) {
-        EJ_HIP(hipMemcpyAsync(len.data(), pp.d_len, 4ull * n, hipMemcpyDeviceToHost, ctx->stream));
+        EJ_HIP(hipMemcpyAsync(slen.data(), pp.d_perm_len, 4ull * n, hipMemcpyDeviceToHost,
+                              ctx->stream));
         sync(ctx);
     }
-    const uint64_t N = pp.maxlen;
-    const uint64_t G = p.K == 0 ? N + 1 : std::max<uint64_t>(1, (N + p.K - 1) / p.K - 1);
+    std::vector<LenGroup> groups = length_groups(slen, p);
     const uint32_t NT = p.r * p.z;
     tm.mark();  // 1: the groups' front ends follow
     // the grouping's own buffers ("grp_*") must not share a name with the
@@ -786,20 +892,94 @@ void join_grouped_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_
     uint64_t raw = 0, ucount = 0, ucap = 0;
     uint64_t *uni = nullptr;
     int which = 0;  // the union grows into two alternating buffers
-    std::vector<uint32_t> ids;
-    std::vector<uint64_t> soff;
-    for (uint64_t g = 0; g < G; g++) {
-        ids.clear();
-        soff.assign(1, 0);
-        uint64_t Ng = 0;
-        for (uint32_t i = 0; i < n; i++)
-            if (in_group(len[i], g, p.K)) {
-                ids.push_back(i);
-                soff.push_back(soff.back() + len[i]);
-                Ng = std::max<uint64_t>(Ng, len[i]);
+    auto append = [&](const uint64_t *gp, uint64_t gc, const uint32_t *d_ids) {
+        if (!gc) return;
+        if (ucount + gc > ucap) {
+            const uint64_t cap = std::max<uint64_t>(2 * ucap, ucount + gc);
+            uint64_t *nb = ws<uint64_t>(ctx, which ? "grp_unionA" : "grp_unionB", cap);
+            if (ucount)
+                EJ_HIP(hipMemcpyAsync(nb, uni, 8 * ucount, hipMemcpyDeviceToDevice, ctx->stream));
+            uni = nb;
+            ucap = cap;
+            which ^= 1;
+        }
+        hipLaunchKernelGGL(k_map_pairs, dim3(grid_for(ctx, gc, 256)), dim3(256), 0, ctx->stream,
+                           gp, gc, d_ids, uni + ucount);
+        EJ_CHECK_LAUNCH();
+        ucount += gc;
+    };
+    // groups [i, j)'s descriptors on the device: starts, places, walk lengths,
+    // and chunks of 64 entries, longest walks first
+    std::vector<uint32_t> desc;
+    const uint32_t *d_gstart = nullptr, *d_glo = nullptr, *d_gL = nullptr;
+    const uint4 *d_chunks = nullptr;
+    uint32_t nchunks = 0;
+    auto describe = [&](size_t i, size_t j) {
+        const size_t ng = j - i, head = (3 * ng + 1 + 3) & ~(size_t)3;
+        desc.assign(head, 0);
+        nchunks = 0;
+        for (size_t g = 0; g < ng; g++) {
+            desc[g + 1] = desc[g] + groups[i + g].k;
+            desc[ng + 1 + g] = groups[i + g].lo;
+            desc[2 * ng + 1 + g] = groups[i + g].L;
+        }
+        for (size_t g = ng; g-- > 0;)  // lengths ascend with the groups
+            for (uint32_t c = 0; c < groups[i + g].k; c += 64) {
+                const uint32_t x[4] = {desc[g] + c, std::min(64u, groups[i + g].k - c),
+                                       (uint32_t)g, 0};
+                desc.insert(desc.end(), x, x + 4);
+                nchunks++;
             }
-        const uint32_t k = (uint32_t)ids.size();
-        if (k < 2) continue;
+        uint32_t *d = ws<uint32_t>(ctx, "grp_desc", desc.size());
+        EJ_HIP(hipMemcpyAsync(d, desc.data(), 4 * desc.size(), hipMemcpyHostToDevice, ctx->stream));
+        d_gstart = d;
+        d_glo = d + ng + 1;
+        d_gL = d + 2 * ng + 1;
+        d_chunks = (const uint4 *)(d + head);
+    };
+    // which groups share the set's alphabet
+    uint64_t members = 0;
+    for (const LenGroup &g : groups) members += g.k;
+    if (ctx->ex.active || members >= 0xFFFFFFFFull) {
+        for (LenGroup &g : groups) g.own = true;
+    } else if (!groups.empty() && pp.sigma) {
+        describe(0, groups.size());
+        std::vector<uint32_t> hmask(8 * groups.size());
+        uint32_t *gmask = ws<uint32_t>(ctx, "grp_mask", hmask.size());
+        EJ_HIP(hipMemsetAsync(gmask, 0, 4 * hmask.size(), ctx->stream));
+        hipLaunchKernelGGL(k_group_alphabet, dim3(nchunks), dim3(64), 0, ctx->stream,
+                           (const uint8_t *)pp.d_codes, d_offsets, pp.base,
+                           (const uint32_t *)pp.d_perm, d_gstart, d_glo, d_chunks, pp.sigma,
+                           gmask);
+        EJ_CHECK_LAUNCH();
+        EJ_HIP(hipMemcpyAsync(hmask.data(), gmask, 4 * hmask.size(), hipMemcpyDeviceToHost,
+                              ctx->stream));
+        sync(ctx);
+        for (size_t g = 0; g < groups.size(); g++) {
+            uint32_t letters = 0;
+            for (int w = 0; w < 8; w++)
+                letters += (uint32_t)__builtin_popcount(hmask[8 * g + w]);
+            groups[g].own = letters != pp.sigma;
+        }
+    }
+    // a group with a front end of its own
+    std::vector<uint32_t> perm, ids;
+    std::vector<uint64_t> soff;
+    auto run_own = [&](const LenGroup &grp) {
+        if (perm.empty()) {
+            perm.resize(n);
+            EJ_HIP(hipMemcpyAsync(perm.data(), pp.d_perm, 4ull * n, hipMemcpyDeviceToHost,
+                                  ctx->stream));
+            sync(ctx);
+            std::vector<uint32_t> len(n);
+            for (uint32_t i = 0; i < n; i++) len[perm[i]] = slen[i];
+            slen.swap(len);  // by position from here on
+        }
+        const uint32_t k = grp.k;
+        ids.assign(perm.begin() + grp.lo, perm.begin() + grp.lo + k);
+        std::sort(ids.begin(), ids.end());
+        soff.assign(1, 0);
+        for (uint32_t i : ids) soff.push_back(soff.back() + slen[i]);
         uint32_t *d_ids = ws<uint32_t>(ctx, "grp_ids", k);
         uint64_t *d_soff = ws<uint64_t>(ctx, "grp_soff", (uint64_t)k + 1);
         uint8_t *d_sub = ws<uint8_t>(ctx, "grp_chars", soff.back() + 16);
@@ -810,10 +990,8 @@ void join_grouped_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_
                            ctx->stream, d_chars, d_offsets, (const uint32_t *)d_ids, k,
                            (const uint64_t *)d_soff, d_sub);
         EJ_CHECK_LAUNCH();
-        const uint64_t Lg = p.L ? p.L : std::max<uint64_t>(1, 3 * Ng);
-        if (Lg > 0x7FFFFFFFull) fail(EJ_EUNSUPPORTED, "group walk length too large");
         Prep pg;
-        prepare(ctx, d_sub, d_soff, k, (uint32_t)Lg, pg, "g");
+        prepare(ctx, d_sub, d_soff, k, grp.L, pg, "g");
         Rand rd;
         draw_randomness(ctx, p, pg.L, pg.sigma, rd, "g");
         uint64_t *keys = ws<uint64_t>(ctx, "g_keys", (uint64_t)NT * k);
@@ -827,21 +1005,62 @@ void join_grouped_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_
         uint64_t graw = 0;
         const uint64_t gc = candidates(ctx, keys, bk, pg.d_len, p.K, &gp, &graw, "g");
         raw += graw;
-        if (!gc) continue;
-        if (ucount + gc > ucap) {
-            const uint64_t cap = std::max<uint64_t>(2 * ucap, ucount + gc);
-            uint64_t *nb = ws<uint64_t>(ctx, which ? "grp_unionA" : "grp_unionB", cap);
-            if (ucount)
-                EJ_HIP(hipMemcpyAsync(nb, uni, 8 * ucount, hipMemcpyDeviceToDevice, ctx->stream));
-            uni = nb;
-            ucap = cap;
-            which ^= 1;
-        }
-        hipLaunchKernelGGL(k_map_pairs, dim3(grid_for(ctx, gc, 256)), dim3(256), 0, ctx->stream,
-                           (const uint64_t *)gp, gc, (const uint32_t *)d_ids, uni + ucount);
-        EJ_CHECK_LAUNCH();
-        ucount += gc;
+        append(gp, gc, d_ids);
         sync(ctx);  // the host vectors of this group are reused by the next
+    };
+    // groups [i, j) through one front end
+    const uint64_t span = (uint64_t)pp.maxlen + p.K + 1;
+    auto run_shared = [&](size_t i, size_t j, uint32_t entries) {
+        const uint32_t ng = (uint32_t)(j - i);
+        describe(i, j);
+        uint32_t *d_ids = ws<uint32_t>(ctx, "grp_ids", entries);
+        uint32_t *d_len = ws<uint32_t>(ctx, "grp_len", entries);
+        hipLaunchKernelGGL(k_group_entries, dim3(grid_for(ctx, entries, 256)), dim3(256), 0,
+                           ctx->stream, (const uint32_t *)pp.d_perm,
+                           (const uint32_t *)pp.d_perm_len, d_gstart, d_glo, ng, entries,
+                           (uint32_t)span, d_ids, d_len);
+        EJ_CHECK_LAUNCH();
+        Rand rd;
+        draw_randomness(ctx, p, groups[j - 1].L, pp.sigma, rd, "g");
+        draw_group_samples(ctx, p, d_gL, ng, rd, "g");
+        Prep pe = pp;
+        pe.n = entries;
+        pe.L = groups[j - 1].L;
+        pe.d_perm = d_ids;
+        const uint64_t tot = (uint64_t)NT * entries;
+        uint64_t *keys = ws<uint64_t>(ctx, "g_keys", tot);
+        const uint32_t kb = bucket_key_bits(ctx, entries, 0);
+        uint32_t *bdk = nullptr, *bids = nullptr;
+        bucket_inputs(ctx, tot, "g", &bdk, &bids);
+        embed_keys(ctx, pe, rd, keys, nullptr, bdk, bids, 61u - kb, d_chunks, nchunks);
+        Buckets bk;
+        bucket(ctx, keys, d_len, nullptr, entries, NT, kb, bk, "g", false, true, false);
+        uint64_t *gp = nullptr;
+        uint64_t graw = 0;
+        const uint64_t gc = candidates(ctx, keys, bk, d_len, p.K, &gp, &graw, "g");
+        raw += graw;
+        append(gp, gc, d_ids);
+        sync(ctx);  // the descriptors are reused by the next batch
+    };
+    for (size_t i = 0, j; i < groups.size(); i = j) {
+        j = i + 1;
+        if (groups[i].own) {
+            run_own(groups[i]);
+            continue;
+        }
+        // A batch ends where its buffers would pass about 2 GB (50 bytes per
+        // table and entry, 12 per group and sample), its lengths 31 bits, or
+        // where walks get too long to keep their records.
+        uint64_t entries = groups[i].k;
+        const bool rec = groups[i].L <= EMBED_REC_STEPS;
+        while (j < groups.size() && !groups[j].own && rec == (groups[j].L <= EMBED_REC_STEPS) &&
+               NT * (entries + groups[j].k) <= 1ull << 25 &&
+               (uint64_t)(j + 1 - i) * NT * p.m <= 1ull << 24 &&
+               (j + 1 - i) * span < 0x7FFFFFFFull) {
+            entries += groups[j].k;
+            j++;
+        }
+        run_shared(i, j, (uint32_t)entries);
     }
     out->L = p.L;  // 0: each group walked 3 x its longest string
     tm.mark();  // 2
