@@ -78,15 +78,61 @@ __global__ void k_sorted_attrs_full(const uint64_t *__restrict__ keys,
     }
 }
 
+// The first of the n sorted values that is not below `top`.  The values are
+// the top bits of hashes, so a value's place is close to its share of the
+// range: three interpolations come within a few entries of it, and a search
+// in doubling steps from there finds it in any case (values that are not
+// spread evenly, long runs of one value, cost more steps of that search).
+__device__ inline uint32_t probe_lower(const uint32_t *__restrict__ d, uint32_t n, uint32_t top) {
+    uint32_t lo = 0, hi = n;  // below `top` before lo, not below it from hi on
+    uint32_t x = __umulhi(top, n);
+    bool less = false;
+    for (int it = 0; it < 3 && lo < hi; it++) {
+        const uint32_t v = d[x];
+        less = v < top;
+        if (less) lo = x + 1; else hi = x;
+        if (lo >= hi) break;
+        const int64_t y = (int64_t)x + (((int64_t)top - (int64_t)v) * (int64_t)n >> 32);
+        x = (uint32_t)min(max(y, (int64_t)lo), (int64_t)hi - 1);
+    }
+    uint32_t step = 2;
+    if (less) {
+        while (hi - lo > step) {
+            if (d[lo + step] >= top) {
+                hi = lo + step;
+                break;
+            }
+            lo += step + 1;
+            step *= 4;
+        }
+    } else {
+        while (hi - lo > step) {
+            if (d[hi - 1 - step] < top) {
+                lo = hi - step;
+                break;
+            }
+            hi -= step + 1;
+            step *= 4;
+        }
+    }
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if (d[mid] < top) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
 // One thread per (table, query): candidates are the entries of the table
 // with the query's full key whose length is within K_q of the query's.
-template <bool EMIT>
-__global__ void k_query_probe(const uint64_t *__restrict__ qkeys, const uint32_t *__restrict__ qlen,
+// Counts them and notes where the first entry of fitting length is.
+// Bound by random 64-byte reads (about 100 G/s on the chip): 4,096 queries in
+// 256 tables of 100,000 entries took 340 us with two binary searches over the
+// whole table, and as much again to emit, which now starts at `first`.
+__global__ void k_query_count(const uint64_t *__restrict__ qkeys, const uint32_t *__restrict__ qlen,
                               const uint32_t *__restrict__ Kq, uint32_t nq,
                               const uint32_t *__restrict__ dk, const uint64_t *__restrict__ key_s,
-                              const uint32_t *__restrict__ len_s, const uint32_t *__restrict__ ids,
-                              uint32_t n, uint32_t T, uint32_t B, uint64_t *__restrict__ counts,
-                              const uint64_t *__restrict__ offs, uint64_t *__restrict__ out) {
+                              const uint32_t *__restrict__ len_s, uint32_t n, uint32_t T,
+                              uint64_t *__restrict__ counts, uint32_t *__restrict__ first) {
     const uint64_t tot = (uint64_t)T * nq;
     for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e < tot;
          e += (uint64_t)gridDim.x * blockDim.x) {
@@ -96,36 +142,56 @@ __global__ void k_query_probe(const uint64_t *__restrict__ qkeys, const uint32_t
         const uint32_t *d = dk + (uint64_t)t * n;
         const uint64_t *ks = key_s + (uint64_t)t * n;
         const uint32_t *ls = len_s + (uint64_t)t * n;
-        // [lo, hi): entries whose top bits equal the query's
-        uint32_t lo = 0, hi = n;
-        while (lo < hi) {
-            uint32_t mid = (lo + hi) >> 1;
-            if (d[mid] < top) lo = mid + 1; else hi = mid;
-        }
-        uint32_t g0 = lo;
-        hi = n;
-        while (lo < hi) {
-            uint32_t mid = (lo + hi) >> 1;
-            if (d[mid] <= top) lo = mid + 1; else hi = mid;
-        }
-        const uint32_t g1 = lo;
-        const uint32_t lq = qlen[q], kq = Kq[q];
-        const uint32_t lmin = lq > kq ? lq - kq : 0u;
-        const uint64_t lmax = (uint64_t)lq + kq;
-        lo = g0;
-        hi = g1;
-        while (lo < hi) {  // first entry of the group with length >= lmin
-            uint32_t mid = (lo + hi) >> 1;
-            if (ls[mid] < lmin) lo = mid + 1; else hi = mid;
-        }
-        uint64_t c = 0, o = EMIT ? offs[e] : 0;
-        for (uint32_t x = lo; x < g1 && (uint64_t)ls[x] <= lmax; x++) {
-            if (ks[x] == key) {
-                if (EMIT) out[o + c] = ((uint64_t)q << B) | ids[(uint64_t)t * n + x];
-                c++;
+        uint64_t c = 0;
+        uint32_t lo = probe_lower(d, n, top);
+        if (lo < n && d[lo] == top) {
+            // the end of the entries with the query's top bits
+            uint32_t g1 = lo + 1, hi = n, step = 2;
+            while (hi - g1 > step) {
+                if (d[g1 + step] > top) {
+                    hi = g1 + step;
+                    break;
+                }
+                g1 += step + 1;
+                step *= 4;
             }
+            while (g1 < hi) {
+                const uint32_t mid = g1 + (hi - g1) / 2;
+                if (d[mid] <= top) g1 = mid + 1; else hi = mid;
+            }
+            const uint32_t lq = qlen[q], kq = Kq[q];
+            const uint32_t lmin = lq > kq ? lq - kq : 0u;
+            const uint64_t lmax = (uint64_t)lq + kq;
+            hi = g1;
+            while (lo < hi) {  // first entry of the group with length >= lmin
+                const uint32_t mid = (lo + hi) >> 1;
+                if (ls[mid] < lmin) lo = mid + 1; else hi = mid;
+            }
+            for (uint32_t x = lo; x < g1 && (uint64_t)ls[x] <= lmax; x++)
+                c += ks[x] == key ? 1u : 0u;
         }
-        if (!EMIT) counts[e] = c;
+        counts[e] = c;
+        first[e] = lo;
+    }
+}
+
+// The counted candidates' codes (q << B | id), from offs[e] on.
+template <typename C>
+__global__ void k_query_emit(const uint64_t *__restrict__ qkeys, uint32_t nq,
+                             const uint64_t *__restrict__ key_s, const uint32_t *__restrict__ ids,
+                             uint32_t n, uint32_t T, uint32_t B, const uint64_t *__restrict__ offs,
+                             const uint32_t *__restrict__ first, uint64_t raw,
+                             C *__restrict__ out) {
+    const uint64_t tot = (uint64_t)T * nq;
+    for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e < tot;
+         e += (uint64_t)gridDim.x * blockDim.x) {
+        uint64_t o = offs[e];
+        const uint64_t end = e + 1 < tot ? offs[e + 1] : raw;
+        if (o == end) continue;
+        const uint32_t t = (uint32_t)(e / nq), q = (uint32_t)(e % nq);
+        const uint64_t key = qkeys[(uint64_t)t * nq + q];
+        for (uint64_t x = (uint64_t)t * n + first[e]; o < end; x++)
+            if (key_s[x] == key) out[o++] = ((C)q << B) | (C)ids[x];
     }
 }
 
@@ -206,7 +272,8 @@ __global__ void k_append_offsets(const uint64_t *__restrict__ off, uint32_t n, u
         out[e] = off[e] - base + shift;
 }
 
-__global__ void k_uniq_flags(const uint64_t *__restrict__ codes, uint64_t cnt,
+template <typename C>
+__global__ void k_uniq_flags(const C *__restrict__ codes, uint64_t cnt,
                              uint32_t *__restrict__ flags) {
     for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e < cnt;
          e += (uint64_t)gridDim.x * blockDim.x)
@@ -215,7 +282,8 @@ __global__ void k_uniq_flags(const uint64_t *__restrict__ codes, uint64_t cnt,
 
 // Unique (q << B | id) codes -> verification pairs (id << 32 | q) and the
 // threshold of each pair.
-__global__ void k_to_pairs(const uint64_t *__restrict__ codes, uint64_t cnt, uint32_t B,
+template <typename C>
+__global__ void k_to_pairs(const C *__restrict__ codes, uint64_t cnt, uint32_t B,
                            const uint32_t *__restrict__ flags, const uint32_t *__restrict__ pos,
                            const uint32_t *__restrict__ Kq, uint64_t *__restrict__ pairs,
                            uint32_t *__restrict__ pk) {
@@ -574,12 +642,15 @@ ej_status ej_query_batch(ej_index *ix, const uint8_t *q, const uint64_t *q_offse
         const uint64_t tot = (uint64_t)T * nq;
         uint64_t *counts = ws<uint64_t>(ctx, "q_counts", tot);
         uint64_t *d_raw = ws<uint64_t>(ctx, "q_raw", 1);
-        const uint32_t B = std::max(1u, std::max(bits_for(ix->n ? ix->n - 1 : 0), bits_for(nq - 1)));
-        hipLaunchKernelGGL(k_query_probe<false>, dim3(grid_for(ctx, tot, 256)), dim3(256), 0,
-                           ctx->stream, (const uint64_t *)qkeys, (const uint32_t *)pq.d_len,
+        uint32_t *first = ws<uint32_t>(ctx, "q_first", tot);
+        // codes: the query above B bits of the index position
+        const uint32_t B = std::max(1u, bits_for(ix->n ? ix->n - 1 : 0));
+        const uint32_t code_bits = B + std::max(1u, bits_for(nq - 1));
+        hipLaunchKernelGGL(k_query_count, dim3(grid_for(ctx, tot, 256)), dim3(256), 0, ctx->stream,
+                           (const uint64_t *)qkeys, (const uint32_t *)pq.d_len,
                            (const uint32_t *)dK, nq, (const uint32_t *)ix->d_dk,
-                           (const uint64_t *)ix->d_key_s, (const uint32_t *)ix->d_len_s,
-                           (const uint32_t *)ix->d_ids, ix->n, T, B, counts, nullptr, nullptr);
+                           (const uint64_t *)ix->d_key_s, (const uint32_t *)ix->d_len_s, ix->n, T,
+                           counts, first);
         EJ_CHECK_LAUNCH();
         scan_exclusive_u64(ctx, counts, counts, tot, d_raw);
         uint64_t raw = 0;
@@ -591,31 +662,42 @@ ej_status ej_query_batch(ej_index *ix, const uint8_t *q, const uint64_t *q_offse
         uint32_t *pk = nullptr;
         if (raw) {
             if (raw >= 0xFFFFFFFFull) fail(EJ_EUNSUPPORTED, "more than 2^32 raw query candidates");
-            uint64_t *rb = ws<uint64_t>(ctx, "q_rawbuf", raw);
-            uint64_t *sorted = ws<uint64_t>(ctx, "q_sorted", raw);
-            hipLaunchKernelGGL(k_query_probe<true>, dim3(grid_for(ctx, tot, 256)), dim3(256), 0,
-                               ctx->stream, (const uint64_t *)qkeys, (const uint32_t *)pq.d_len,
-                               (const uint32_t *)dK, nq, (const uint32_t *)ix->d_dk,
-                               (const uint64_t *)ix->d_key_s, (const uint32_t *)ix->d_len_s,
-                               (const uint32_t *)ix->d_ids, ix->n, T, B, nullptr,
-                               (const uint64_t *)counts, rb);
-            EJ_CHECK_LAUNCH();
-            radix_sort_u64(ctx, rb, sorted, raw, 2 * B, ctx->tune.radix_bits);
             uint32_t *flags = ws<uint32_t>(ctx, "q_uflags", raw);
             uint32_t *pos = ws<uint32_t>(ctx, "q_upos", raw);
             uint64_t *d_cnt = ws<uint64_t>(ctx, "q_ucnt", 1);
-            hipLaunchKernelGGL(k_uniq_flags, dim3(grid_for(ctx, raw, 256)), dim3(256), 0,
-                               ctx->stream, (const uint64_t *)sorted, raw, flags);
-            EJ_CHECK_LAUNCH();
-            scan_exclusive_u32(ctx, flags, pos, raw, d_cnt);
-            read_back(ctx, d_cnt, 8, &cnt);
-            pairs = ws<uint64_t>(ctx, "q_pairs", cnt);
-            pk = ws<uint32_t>(ctx, "q_pk", cnt);
-            hipLaunchKernelGGL(k_to_pairs, dim3(grid_for(ctx, raw, 256)), dim3(256), 0,
-                               ctx->stream, (const uint64_t *)sorted, raw, B,
-                               (const uint32_t *)flags, (const uint32_t *)pos,
-                               (const uint32_t *)dK, pairs, pk);
-            EJ_CHECK_LAUNCH();
+            auto unique_pairs = [&](auto *rb, auto *sorted) {
+                using C = std::remove_pointer_t<decltype(rb)>;
+                hipLaunchKernelGGL(k_query_emit<C>, dim3(grid_for(ctx, tot, 256)), dim3(256), 0,
+                                   ctx->stream, (const uint64_t *)qkeys, nq,
+                                   (const uint64_t *)ix->d_key_s, (const uint32_t *)ix->d_ids,
+                                   ix->n, T, B, (const uint64_t *)counts,
+                                   (const uint32_t *)first, raw, rb);
+                EJ_CHECK_LAUNCH();
+                if constexpr (sizeof(C) == 4)
+                    radix_sort_u32(ctx, rb, nullptr, sorted, nullptr, 1, (uint32_t)raw, code_bits,
+                                   ctx->tune.radix_bits);
+                else
+                    radix_sort_u64(ctx, rb, sorted, raw, code_bits, ctx->tune.radix_bits);
+                hipLaunchKernelGGL(k_uniq_flags<C>, dim3(grid_for(ctx, raw, 256)), dim3(256), 0,
+                                   ctx->stream, (const C *)sorted, raw, flags);
+                EJ_CHECK_LAUNCH();
+                scan_exclusive_u32(ctx, flags, pos, raw, d_cnt);
+                read_back(ctx, d_cnt, 8, &cnt);
+                pairs = ws<uint64_t>(ctx, "q_pairs", cnt);
+                pk = ws<uint32_t>(ctx, "q_pk", cnt);
+                hipLaunchKernelGGL(k_to_pairs<C>, dim3(grid_for(ctx, raw, 256)), dim3(256), 0,
+                                   ctx->stream, (const C *)sorted, raw, B,
+                                   (const uint32_t *)flags, (const uint32_t *)pos,
+                                   (const uint32_t *)dK, pairs, pk);
+                EJ_CHECK_LAUNCH();
+            };
+            // (32-bit codes up to 65,536 queries on 65,536 strings, and the like)
+            uint64_t *rb = ws<uint64_t>(ctx, "q_rawbuf", raw);
+            uint64_t *sorted = ws<uint64_t>(ctx, "q_sorted", raw);
+            if (code_bits <= 32)
+                unique_pairs((uint32_t *)rb, (uint32_t *)sorted);
+            else
+                unique_pairs(rb, sorted);
         }
         out->n_candidates = cnt;
         need += verify_bytes(ctx, cnt, qtotal, nq, ix->sigma, Kmax);
@@ -645,7 +727,8 @@ ej_status ej_query_batch(ej_index *ix, const uint8_t *q, const uint64_t *q_offse
             sx.masks = ix->masks;
             sx.planes = ix->d_planes;
             const VerifySet sq = verify_set(pq, dqo, "qm");
-            verify(ctx, ix->sigma, sx, &sq, pairs, cnt, 0, pk, dist);
+            verify(ctx, ix->sigma, sx, &sq, pairs, cnt, 0, pk, dist, nullptr, nullptr, nullptr, 0,
+                   Kmax);
             uint32_t *flags = ws<uint32_t>(ctx, "q_oflags", cnt);
             uint32_t *pos = ws<uint32_t>(ctx, "q_opos", cnt);
             uint64_t *d_no = ws<uint64_t>(ctx, "q_nout", 1);

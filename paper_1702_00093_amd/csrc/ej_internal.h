@@ -399,7 +399,7 @@ void verify(ej_ctx *ctx, uint32_t sigma, VerifySet A, const VerifySet *B,
             const uint64_t *d_pairs, uint64_t count, uint32_t K, const uint32_t *d_Kq,
             int32_t *d_dist, unsigned long long *d_columns = nullptr,
             const uint32_t *d_order = nullptr, const uint64_t *d_count = nullptr,
-            uint32_t minlen = 0);
+            uint32_t minlen = 0, uint32_t Kq_max = 0);
 
 // Bit planes of a code array: plane_count(sigma) words per 32 letters.
 uint32_t plane_count(uint32_t sigma);

@@ -600,18 +600,29 @@ __global__ void k_strip_init(uint32_t *__restrict__ ctr, uint32_t n, uint32_t cl
     }
 }
 
-// Thresholds per pair: the class of each pair's own threshold.
-__global__ void __launch_bounds__(256)
+// Thresholds per pair: the class of each pair's own threshold.  A workgroup
+// counts its 1,024 pairs in LDS and takes its places in the lists with one
+// atomic per class (one per wave and class took 26 us for 50,000 pairs: the
+// counters share two cache lines).
+__global__ void __launch_bounds__(1024)
     k_strip_widths(const uint32_t *__restrict__ Kq, uint64_t first, uint64_t count,
                    const uint64_t *__restrict__ count_dev, uint32_t *__restrict__ ctr,
                    uint32_t *__restrict__ lists, uint64_t cap) {
+    __shared__ uint32_t cnt[CTR], at[CTR];
     uint64_t live = count;
     if (count_dev) live = *count_dev > first ? min(*count_dev - first, count) : 0;
-    const uint32_t lane = threadIdx.x & 63u;
-    for (uint64_t b = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) & ~63ull; b < live;
-         b += (uint64_t)gridDim.x * blockDim.x) {
-        const uint64_t k = b + lane;
-        strip_append(k < live ? (Kq[k] + 33u) / 32u : 0u, (uint32_t)k, ctr, lists, cap);
+    for (uint64_t b = (uint64_t)blockIdx.x * 1024; b < live; b += (uint64_t)gridDim.x * 1024) {
+        if (threadIdx.x < CTR) cnt[threadIdx.x] = 0;
+        __syncthreads();
+        const uint64_t k = b + threadIdx.x;
+        const uint32_t c = k < live ? width_class((Kq[k] + 33u) / 32u) : 0u;
+        const uint32_t rank = c ? atomicAdd(&cnt[c], 1u) : 0u;
+        __syncthreads();
+        if (threadIdx.x < CTR && cnt[threadIdx.x])
+            at[threadIdx.x] = atomicAdd(&ctr[threadIdx.x], cnt[threadIdx.x]);
+        __syncthreads();
+        if (c) lists[list_at(c, (uint64_t)at[c] + rank, cap)] = (uint32_t)k;
+        __syncthreads();
     }
 }
 
@@ -704,7 +715,14 @@ void verify_strips(ej_ctx *ctx, uint32_t sigma, const StripSet &A, const StripSe
     // of the survivors ran at one wave each, 4.15 ms for the workload above
     // against 3.94; 256 lanes measured the same as 128.
     const uint32_t fill = (uint32_t)ctx->num_cu * 4 * 128;
-    for (uint64_t e = first;; e += std::max<uint64_t>(1024, (e / 2) & ~31ull)) {
+    // Thresholds per pair: also at a half and a quarter of the first end, for
+    // the pairs of smaller thresholds, down to 256 columns (49,000 pairs,
+    // thresholds of 90 to 550: 1.27 -> 1.06 ms; of 10 to 180, strips of 96 and
+    // 192 columns cost 40 us more than they saved).
+    uint64_t e = first;
+    for (int i = 0; i < 2 && d_Kq && e >= 512; i++) e = (e / 2 + 31) & ~31ull;
+    for (;; e = e < first ? std::min(2 * e, first)
+                          : e + std::max<uint64_t>(1024, (e / 2) & ~31ull)) {
         // (a band in 16 lanes gains nothing from being narrower)
         if (e >= mtext || count * 16 <= fill) {
             end.push_back(0xFFFFFFFFu);
@@ -736,7 +754,7 @@ void verify_strips(ej_ctx *ctx, uint32_t sigma, const StripSet &A, const StripSe
         EJ_CHECK_LAUNCH();
         const uint32_t *kq = d_Kq ? d_Kq + b0 : nullptr;
         if (d_Kq) {
-            hipLaunchKernelGGL(k_strip_widths, dim3(grid_for(ctx, n, 256)), dim3(256), 0,
+            hipLaunchKernelGGL(k_strip_widths, dim3(grid_for(ctx, n, 1024)), dim3(1024), 0,
                                ctx->stream, kq, b0, n, d_count, ctr, lists[0], batch);
             EJ_CHECK_LAUNCH();
         }

@@ -1882,11 +1882,13 @@ void build_masks(ej_ctx *ctx, const uint8_t *d_codes, const uint64_t *d_offsets,
 void verify(ej_ctx *ctx, uint32_t sigma, VerifySet SA, const VerifySet *setB,
             const uint64_t *d_pairs, uint64_t count, uint32_t K, const uint32_t *d_Kq,
             int32_t *d_dist, unsigned long long *d_columns, const uint32_t *d_order,
-            const uint64_t *d_count, uint32_t minlen) {
+            const uint64_t *d_count, uint32_t minlen, uint32_t Kq_max) {
     if (count == 0) return;
     if (count >= 0xFFFFFFFFull) fail(EJ_EUNSUPPORTED, "more than 2^32 pairs in one verification");
     uint32_t Kmax = K;
-    if (d_Kq) {
+    if (d_Kq && Kq_max && strip_form(ctx)) {
+        Kmax = Kq_max;  // the caller's bound (the strips go by each pair's own threshold)
+    } else if (d_Kq) {
         uint32_t *d_mx = ws<uint32_t>(ctx, "verify_kmax", 1);
         EJ_HIP(hipMemsetAsync(d_mx, 0, 4, ctx->stream));
         hipLaunchKernelGGL(k_max_u32, dim3(grid_for(ctx, count, 256)), dim3(256), 0, ctx->stream,

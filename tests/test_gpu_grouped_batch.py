@@ -11,6 +11,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.fixture(scope="module")
 def ctx():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
     import paper_1702_00093_amd as ej
     ej.lib()
     return ej.Context(0)

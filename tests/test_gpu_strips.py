@@ -14,6 +14,8 @@ BYTES = bytes(range(40, 90))  # 50 letters: 8 planes
 
 @pytest.fixture(scope="module")
 def ctx():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
     import paper_1702_00093_amd as ej
     ej.lib()
     return ej.Context(0)
