@@ -175,6 +175,7 @@ ej_status ej_create(ej_ctx **out, int device, void *hip_stream) {
         EJ_HIP(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device));
         ctx->lds_max = lds;
         EJ_HIP(hipHostMalloc((void **)&ctx->pinned, 4096, hipHostMallocDefault));
+        EJ_HIP(hipMalloc((void **)&ctx->survey, (size_t)ctx->num_cu * SURVEY_BYTES));
         static_scratch_init(device);
         for (int i = 0; i < 8; i++) EJ_HIP(hipEventCreate(&ctx->timers.ev[i]));
         for (int i = 0; i < 4; i++) EJ_HIP(hipEventCreate(&ctx->timers.kv[i]));
@@ -201,6 +202,7 @@ void ej_destroy(ej_ctx *ctx) {
     for (auto &kv : ctx->graphs) (void)hipGraphExecDestroy(kv.second);
     ctx->graphs.clear();
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+    if (ctx->survey) (void)hipFree(ctx->survey);
     if (ctx->pinned_out) (void)hipHostFree(ctx->pinned_out);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;

@@ -31,26 +31,37 @@ struct PrepInfo {
     uint32_t maxlen;
     uint32_t minlen;
     uint32_t err;       // 1: offsets decrease, 2: string longer than 2^31-1
+    uint32_t pad;
     uint64_t off0, offn;
 };
 
-__global__ void k_prep_info(const uint64_t *__restrict__ offsets, uint32_t n,
-                            PrepInfo *__restrict__ info) {
-    if (threadIdx.x == 0) {
-        info->off0 = offsets[0];
-        info->offn = offsets[n];
-    }
-    if (threadIdx.x < 8) info->mask[threadIdx.x] = 0;
-    if (threadIdx.x == 8) info->maxlen = 0;
-    if (threadIdx.x == 9) info->err = 0;
-    if (threadIdx.x == 10) info->minlen = 0xFFFFFFFFu;
-}
+// What one workgroup of k_survey has seen.
+struct SurveyPart {
+    uint32_t mask[8];
+    uint32_t maxlen, minlen, err, pad;
+};
 
-__global__ void k_lengths(const uint64_t *__restrict__ offsets, uint32_t n,
-                          uint32_t *__restrict__ len, PrepInfo *__restrict__ info) {
+// First look at a string set, in one launch: the lengths, their extremes, and
+// the presence bitmap of the bytes in [offsets[0], offsets[n]).  Each
+// workgroup leaves its findings in a place of its own (atomics on one word
+// from every wave took 74 us for 200,000 strings).
+//
+// Bytes are read 16 at a time over the aligned body.  Where all 16 are in 64..95
+// (capital letters), each costs a shift and an or into one 32-bit mask; other
+// vectors sort their bytes by class: 64..127 into a 64-bit mask, the rest into
+// the workgroup's mask in LDS.  Bound by reading the text.
+__global__ void __launch_bounds__(256)
+    k_survey(const uint64_t *__restrict__ offsets, uint32_t n, const uint8_t *__restrict__ chars,
+             uint32_t *__restrict__ len, SurveyPart *__restrict__ parts) {
+    __shared__ uint32_t m[8], ext[3];
+    if (threadIdx.x < 8) m[threadIdx.x] = 0;
+    if (threadIdx.x < 3) ext[threadIdx.x] = threadIdx.x == 1 ? 0xFFFFFFFFu : 0u;
+    __syncthreads();
+    const uint64_t tid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
+    const uint64_t nth = (uint64_t)gridDim.x * blockDim.x;
     uint32_t mx = 0, mn = 0xFFFFFFFFu, err = 0;
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        uint64_t a = offsets[i], b = offsets[i + 1];
+    for (uint64_t i = tid; i < n; i += nth) {
+        const uint64_t a = offsets[i], b = offsets[i + 1];
         uint64_t l = 0;
         if (b < a)
             err |= 1u;
@@ -64,53 +75,34 @@ __global__ void k_lengths(const uint64_t *__restrict__ offsets, uint32_t n,
         mx = l > mx ? (uint32_t)l : mx;
         mn = l < mn ? (uint32_t)l : mn;
     }
-    // wave reduction then one atomic per wave
-    for (int d = 32; d >= 1; d >>= 1) {
-        mx = max(mx, (uint32_t)__shfl_xor((int)mx, d, 64));
-        mn = min(mn, (uint32_t)__shfl_xor((int)mn, d, 64));
-        err |= (uint32_t)__shfl_xor((int)err, d, 64);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        if (mx) atomicMax(&info->maxlen, mx);
-        if (mn != 0xFFFFFFFFu) atomicMin(&info->minlen, mn);
-        if (err) atomicOr(&info->err, err);
-    }
-}
-
-// Presence bitmap of the bytes in [base, base+total): 16-byte loads over the
-// aligned body, single bytes for the unaligned head and tail.
-__global__ void k_presence(const uint8_t *__restrict__ chars, PrepInfo *__restrict__ info) {
-    // [base, base+total) from the offsets (k_prep_info ran first on the stream);
-    // decreasing offsets are reported through info->err and scan nothing here
-    const uint64_t base = info->off0;
-    const uint64_t total = info->offn >= info->off0 ? info->offn - info->off0 : 0;
-    __shared__ uint32_t m[8];
-    if (threadIdx.x < 8) m[threadIdx.x] = 0;
-    __syncthreads();
+    // decreasing offsets are reported as such and nothing is scanned
+    const uint64_t base = offsets[0], last = offsets[n];
+    const uint64_t total = chars && last >= base ? last - base : 0;
     const uint8_t *p = chars + base;
     const uint64_t start = (uint64_t)(uintptr_t)p;
     uint64_t head = ((start + 15) & ~15ull) - start;
     if (head > total) head = total;
     const uint64_t nbody = (total - head) / 16;
     const uint64_t tail0 = head + nbody * 16;
-    uint32_t loc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    const uint64_t tid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-    const uint64_t nth = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t k = tid; k < head; k += nth) {
-        uint32_t byte = p[k];
-        loc[byte >> 5] |= 1u << (byte & 31);
-    }
-    for (uint64_t k = tail0 + tid; k < total; k += nth) {
-        uint32_t byte = p[k];
-        loc[byte >> 5] |= 1u << (byte & 31);
-    }
-    // the body: bytes 64..127 (letters) go to a 64-bit register mask without
-    // branches; any other byte to the block's LDS mask, one atomic each
+    for (uint64_t k = tid; k < head; k += nth) atomicOr(&m[p[k] >> 5], 1u << (p[k] & 31));
+    for (uint64_t k = tail0 + tid; k < total; k += nth)
+        atomicOr(&m[p[k] >> 5], 1u << (p[k] & 31));
     const uint4 *body = (const uint4 *)(p + head);
+    uint32_t caps = 0;
     uint64_t letters = 0;
-    for (uint64_t c = tid; c < nbody; c += nth) {
-        uint4 v = body[c];
-        uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    auto take = [&](const uint4 &v) {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        uint32_t other = 0, set = 0;
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            other |= (w[q] ^ 0x40404040u) & 0xE0E0E0E0u;
+            set |= (1u << (w[q] & 31)) | (1u << ((w[q] >> 8) & 31)) |
+                   (1u << ((w[q] >> 16) & 31)) | (1u << ((w[q] >> 24) & 31));
+        }
+        if (other == 0) {
+            caps |= set;
+            return;
+        }
 #pragma unroll
         for (int q = 0; q < 16; q++) {
             const uint32_t byte = (w[q >> 2] >> ((q & 3) * 8)) & 0xFFu;
@@ -118,18 +110,77 @@ __global__ void k_presence(const uint8_t *__restrict__ chars, PrepInfo *__restri
             letters |= letter ? (1ull << (byte & 63)) : 0ull;
             if (!letter) atomicOr(&m[byte >> 5], 1u << (byte & 31));
         }
+    };
+    uint64_t c = tid;
+    for (; c + 3 * nth < nbody; c += 4 * nth) {
+        const uint4 v0 = body[c], v1 = body[c + nth], v2 = body[c + 2 * nth],
+                    v3 = body[c + 3 * nth];
+        take(v0);
+        take(v1);
+        take(v2);
+        take(v3);
     }
-    loc[2] |= (uint32_t)letters;
-    loc[3] |= (uint32_t)(letters >> 32);
-#pragma unroll
-    for (int q = 0; q < 8; q++)
-        if (loc[q]) atomicOr(&m[q], loc[q]);
+    for (; c < nbody; c += nth) take(body[c]);
+    caps |= (uint32_t)letters;
+    const uint32_t low = (uint32_t)(letters >> 32);
+    if (caps) atomicOr(&m[2], caps);
+    if (low) atomicOr(&m[3], low);
+    if (mx) atomicMax(&ext[0], mx);
+    if (mn != 0xFFFFFFFFu) atomicMin(&ext[1], mn);
+    if (err) atomicOr(&ext[2], err);
     __syncthreads();
-    // most blocks find nothing new: read first, so that the device-wide
-    // word sees one atomic per new bit pattern instead of one per block
-    if (threadIdx.x < 8 && (m[threadIdx.x] & ~__atomic_load_n(&info->mask[threadIdx.x], __ATOMIC_RELAXED)))
-        atomicOr(&info->mask[threadIdx.x], m[threadIdx.x]);
+    SurveyPart *out = parts + blockIdx.x;
+    if (threadIdx.x < 8) out->mask[threadIdx.x] = m[threadIdx.x];
+    if (threadIdx.x == 8) out->maxlen = ext[0];
+    if (threadIdx.x == 9) out->minlen = ext[1];
+    if (threadIdx.x == 10) out->err = ext[2];
 }
+
+// One workgroup: the parts' sum, straight into pinned host memory.
+__global__ void __launch_bounds__(1024)
+    k_survey_sum(const uint64_t *__restrict__ offsets, uint32_t n,
+                 const SurveyPart *__restrict__ parts, uint32_t nparts,
+                 PrepInfo *__restrict__ info) {
+    __shared__ uint32_t acc[11];
+    if (threadIdx.x < 11) acc[threadIdx.x] = threadIdx.x == 9 ? 0xFFFFFFFFu : 0u;
+    __syncthreads();
+    uint32_t x[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0xFFFFFFFFu, 0};
+    for (uint32_t i = threadIdx.x; i < nparts; i += 1024) {
+        const SurveyPart q = parts[i];
+#pragma unroll
+        for (int w = 0; w < 8; w++) x[w] |= q.mask[w];
+        x[8] = max(x[8], q.maxlen);
+        x[9] = min(x[9], q.minlen);
+        x[10] |= q.err;
+    }
+#pragma unroll
+    for (int w = 0; w < 11; w++) {
+        for (int d = 32; d >= 1; d >>= 1) {
+            const uint32_t y = (uint32_t)__shfl_xor((int)x[w], d, 64);
+            x[w] = w == 8 ? max(x[w], y) : w == 9 ? min(x[w], y) : x[w] | y;
+        }
+        if ((threadIdx.x & 63) == 0) {
+            if (w == 8)
+                atomicMax(&acc[w], x[w]);
+            else if (w == 9)
+                atomicMin(&acc[w], x[w]);
+            else
+                atomicOr(&acc[w], x[w]);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < 8) info->mask[threadIdx.x] = acc[threadIdx.x];
+    if (threadIdx.x == 8) info->maxlen = acc[8];
+    if (threadIdx.x == 9) info->minlen = acc[9];
+    if (threadIdx.x == 10) info->err = acc[10];
+    if (threadIdx.x == 11) info->off0 = offsets[0];
+    if (threadIdx.x == 12) info->offn = offsets[n];
+}
+
+// The alphabet table as a kernel argument: no copy to the device before it.
+struct Alphabet {
+    uint8_t code[256];
+};
 
 // One pass over the characters: thread w maps characters w*CPD ..
 // w*CPD+CPD-1 through the alphabet table, stores their codes (as whole
@@ -138,11 +189,11 @@ __global__ void k_presence(const uint8_t *__restrict__ chars, PrepInfo *__restri
 // 8 packed words, which the walk may read past the end, and 64 code bytes.
 template <int BW>
 __global__ void k_encode_pack(const uint8_t *__restrict__ chars, uint64_t base, uint64_t total,
-                              const uint8_t *__restrict__ lut_g, uint8_t *__restrict__ codes,
+                              Alphabet alphabet, uint8_t *__restrict__ codes,
                               uint64_t nwords, uint32_t *__restrict__ packed) {
     constexpr int CPD = 32 / BW;
     __shared__ uint8_t lut[256];
-    lut[threadIdx.x & 255] = lut_g[threadIdx.x & 255];
+    lut[threadIdx.x & 255] = alphabet.code[threadIdx.x & 255];
     __syncthreads();
     const uint8_t *p = chars + base;
     for (uint64_t w = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; w < nwords + 8;
@@ -200,9 +251,42 @@ __global__ void k_encode_pack(const uint8_t *__restrict__ chars, uint64_t base, 
     }
 }
 
-__global__ void k_iota(uint32_t *__restrict__ a, uint32_t n) {
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        a[i] = i;
+// Input of the length sort: keys and positions.
+__global__ void k_length_keys(const uint32_t *__restrict__ len, uint32_t n,
+                              uint32_t *__restrict__ key, uint32_t *__restrict__ pos) {
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+        key[i] = len[i];
+        pos[i] = i;
+    }
+}
+
+// Length order of a small set by counting, in one launch: string i's place is
+// the number of strings that are shorter, or as long and before it.  64
+// strings per workgroup, the others split over its 16 waves.  The sort takes
+// two passes of three to five launches, 25 to 50 us whatever the size; this
+// takes 4 us for 2,000 strings and as long as the sort near RANK_MAX.
+constexpr uint32_t RANK_MAX = 8192;
+
+__global__ void __launch_bounds__(1024)
+    k_length_rank(const uint32_t *__restrict__ len, uint32_t n, uint32_t *__restrict__ perm,
+                  uint32_t *__restrict__ perm_len) {
+    __shared__ uint32_t below[64];
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (threadIdx.x < 64) below[threadIdx.x] = 0;
+    __syncthreads();
+    const uint32_t i = blockIdx.x * 64 + lane;
+    const uint32_t li = i < n ? len[i] : 0u;
+    const uint32_t per = (n + 15) / 16, j0 = min(wave * per, n), j1 = min(j0 + per, n);
+    uint32_t c = 0;
+#pragma unroll 8
+    for (uint32_t j = j0; j < j1; j++) c += len[j] < li + (j < i ? 1u : 0u) ? 1u : 0u;
+    atomicAdd(&below[lane], c);
+    __syncthreads();
+    if (wave == 0 && i < n) {
+        perm[below[lane]] = i;
+        perm_len[below[lane]] = li;
+    }
 }
 
 // ------------------------------------------------------------ randomness --
@@ -296,6 +380,71 @@ __global__ void k_sample_sort(const uint32_t *__restrict__ pos, uint32_t S,
     atomicMax(&mx, lmx);
     __syncthreads();
     if (threadIdx.x == 0) J[l] = mx;
+}
+
+// All of the above in one launch, for S = z * m up to DRAW_MAX: the first r
+// workgroups draw and sort a seed's samples (in LDS) and draw its vectors, the
+// others draw the random words and, again from the generator, the steps' bits.
+constexpr uint32_t DRAW_MAX = 4096;
+
+__global__ void __launch_bounds__(512)
+    k_draw_all(uint64_t seed, uint32_t r, uint32_t z, uint32_t m, uint32_t L, uint32_t nw,
+               uint32_t Lpad, uint32_t sigma, uint32_t *__restrict__ Rwords,
+               uint32_t *__restrict__ Rstep, uint32_t *__restrict__ pos, uint64_t *__restrict__ v,
+               uint32_t *__restrict__ spos, uint32_t *__restrict__ sslot,
+               uint32_t *__restrict__ J) {
+    extern __shared__ uint32_t p[];  // [S]
+    __shared__ uint32_t mx;
+    const uint32_t S = z * m;
+    if (blockIdx.x < r) {
+        const uint32_t l = blockIdx.x;
+        const size_t row = (size_t)l * S;
+        if (threadIdx.x == 0) mx = 0;
+        __syncthreads();
+        uint32_t lmx = 0;
+        for (uint32_t e = threadIdx.x; e < S; e += blockDim.x) {
+            const uint32_t tbl = l * z + e / m, k = e % m;
+            const uint32_t x =
+                (uint32_t)__umul64hi(rng_word(stream_key(seed, TAG_POS, tbl), k), (uint64_t)L);
+            p[e] = x;
+            pos[row + e] = x;
+            v[row + e] = (rng_word(stream_key(seed, TAG_V, tbl), k) >> 3) % P61;
+            lmx = max(lmx, x + 1);
+        }
+        atomicMax(&mx, lmx);
+        __syncthreads();
+        for (uint32_t e = threadIdx.x; e < S; e += blockDim.x) {
+            const uint32_t pe = p[e];
+            uint32_t rank = 0;
+#pragma unroll 8
+            for (uint32_t f = 0; f < S; f++) rank += p[f] < pe + (f < e ? 1u : 0u) ? 1u : 0u;
+            spos[row + rank] = pe;
+            sslot[row + rank] = e;
+        }
+        if (threadIdx.x == 0) J[l] = mx;
+        return;
+    }
+    const uint64_t first = (uint64_t)(blockIdx.x - r) * blockDim.x + threadIdx.x;
+    const uint64_t stride = (uint64_t)(gridDim.x - r) * blockDim.x;
+    for (uint64_t e = first; e < (uint64_t)r * nw; e += stride) {
+        const uint32_t l = (uint32_t)(e / nw), w = (uint32_t)(e % nw);
+        Rwords[e] = (uint32_t)(rng_word(stream_key(seed, TAG_R, l), w >> 1) >> (32 * (w & 1)));
+    }
+    const uint32_t mask = sigma >= 32 ? 0xFFFFFFFFu : ((1u << sigma) - 1u);
+    for (uint64_t e = first; e < (uint64_t)r * Lpad; e += stride) {
+        const uint32_t l = (uint32_t)(e / Lpad), j = (uint32_t)(e % Lpad);
+        uint32_t val = 0;
+        if (j < L) {
+            // bits j sigma .. j sigma + 31 of the stream
+            const uint64_t key = stream_key(seed, TAG_R, l);
+            const uint64_t b0 = (uint64_t)j * sigma;
+            const uint32_t sh = (uint32_t)(b0 & 63);
+            uint64_t x = rng_word(key, (uint32_t)(b0 >> 6)) >> sh;
+            if (sh > 32) x |= rng_word(key, (uint32_t)(b0 >> 6) + 1) << (64 - sh);
+            val = (uint32_t)x & mask;
+        }
+        Rstep[e] = val;
+    }
 }
 
 // --------------------------------------------------------------- the walk --
@@ -562,22 +711,20 @@ void prepare(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets, uin
     pp.n = n;
     pp.d_offsets = d_offsets;
     pp.d_chars = d_chars;
-    PrepInfo *d_info = ws<PrepInfo>(ctx, t + "_info", 1);
     pp.d_len = ws<uint32_t>(ctx, t + "_len", n + 1);
-    hipLaunchKernelGGL(k_prep_info, dim3(1), dim3(64), 0, ctx->stream, d_offsets, n, d_info);
+    const uint32_t nparts = (uint32_t)ctx->num_cu * SURVEY_PARTS;
+    static_assert(sizeof(SurveyPart) * SURVEY_PARTS == SURVEY_BYTES, "");
+    SurveyPart *parts = (SurveyPart *)ctx->survey;
+    hipLaunchKernelGGL(k_survey, dim3(nparts), dim3(256), 0, ctx->stream, d_offsets, n, d_chars,
+                       pp.d_len, parts);
     EJ_CHECK_LAUNCH();
-    if (n)
-        hipLaunchKernelGGL(k_lengths, dim3(grid_for(ctx, n, 256)), dim3(256), 0, ctx->stream,
-                           d_offsets, n, pp.d_len, d_info);
+    // (pinned host memory is addressed by the device as it is)
+    hipLaunchKernelGGL(k_survey_sum, dim3(1), dim3(1024), 0, ctx->stream, d_offsets, n,
+                       (const SurveyPart *)parts, nparts, (PrepInfo *)ctx->pinned);
     EJ_CHECK_LAUNCH();
-    // the byte presence bitmap in the same round trip as the offsets summary
-    if (d_chars) {
-        hipLaunchKernelGGL(k_presence, dim3((uint32_t)ctx->num_cu * 16), dim3(256), 0,
-                           ctx->stream, d_chars, d_info);
-        EJ_CHECK_LAUNCH();
-    }
+    sync(ctx);
     PrepInfo info;
-    read_back(ctx, d_info, sizeof(PrepInfo), &info);
+    memcpy(&info, ctx->pinned, sizeof(info));
     if (info.err & 1u) fail(EJ_EINVAL, "offsets are not non-decreasing");
     if (info.err & 2u) fail(EJ_EINVAL, "a string is longer than 2^31-1 bytes");
     if (info.offn < info.off0) fail(EJ_EINVAL, "offsets[n] < offsets[0]");
@@ -618,8 +765,8 @@ void prepare(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets, uin
     uint32_t sig_eff = pp.sigma ? pp.sigma : 1;
     pp.bw = sig_eff <= 4 ? 2 : (sig_eff <= 16 ? 4 : 8);
     // encodings
-    uint8_t *d_lut = ws<uint8_t>(ctx, t + "_lut", 256);
-    EJ_HIP(hipMemcpyAsync(d_lut, pp.lut, 256, hipMemcpyHostToDevice, ctx->stream));
+    Alphabet alphabet;
+    memcpy(alphabet.code, pp.lut, 256);
     pp.d_codes = ws<uint8_t>(ctx, t + "_codes", ((pp.total + 3) & ~3ull) + 64);
     uint32_t cpd = 32 / pp.bw;
     uint64_t nwords = (pp.total + cpd - 1) / cpd;
@@ -628,7 +775,7 @@ void prepare(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets, uin
         dim3 g(grid_for(ctx, nwords + 8, 256));
         auto launch = [&](auto kern) {
             hipLaunchKernelGGL(kern, g, dim3(256), 0, ctx->stream, d_chars, pp.base, pp.total,
-                               (const uint8_t *)d_lut, pp.d_codes, nwords, pp.d_packed);
+                               alphabet, pp.d_codes, nwords, pp.d_packed);
             EJ_CHECK_LAUNCH();
         };
         if (pp.bw == 2)
@@ -641,16 +788,20 @@ void prepare(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets, uin
     // length order (stable: ties keep input order)
     pp.d_perm = nullptr;
     if (need_perm && n) {
-        uint32_t *lk = ws<uint32_t>(ctx, t + "_lenkey", n);
-        uint32_t *iota = ws<uint32_t>(ctx, t + "_iota", n);
-        uint32_t *lk2 = ws<uint32_t>(ctx, t + "_lenkey2", n);
+        pp.d_perm_len = ws<uint32_t>(ctx, t + "_lenkey2", n);
         pp.d_perm = ws<uint32_t>(ctx, t + "_perm", n);
-        pp.d_perm_len = lk2;
-        EJ_HIP(hipMemcpyAsync(lk, pp.d_len, n * sizeof(uint32_t), hipMemcpyDeviceToDevice,
-                              ctx->stream));
-        hipLaunchKernelGGL(k_iota, dim3(grid_for(ctx, n, 256)), dim3(256), 0, ctx->stream, iota, n);
-        EJ_CHECK_LAUNCH();
-        radix_sort_u32(ctx, lk, iota, lk2, pp.d_perm, 1, n, bits_for(pp.maxlen), 8);
+        if (n <= RANK_MAX) {
+            hipLaunchKernelGGL(k_length_rank, dim3(ceil_div(n, 64)), dim3(1024), 0, ctx->stream,
+                               (const uint32_t *)pp.d_len, n, pp.d_perm, pp.d_perm_len);
+            EJ_CHECK_LAUNCH();
+        } else {
+            uint32_t *lk = ws<uint32_t>(ctx, t + "_lenkey", n);
+            uint32_t *iota = ws<uint32_t>(ctx, t + "_iota", n);
+            hipLaunchKernelGGL(k_length_keys, dim3(grid_for(ctx, n, 256)), dim3(256), 0,
+                               ctx->stream, (const uint32_t *)pp.d_len, n, lk, iota);
+            EJ_CHECK_LAUNCH();
+            radix_sort_u32(ctx, lk, iota, pp.d_perm_len, pp.d_perm, 1, n, bits_for(pp.maxlen), 8);
+        }
     }
 }
 
@@ -692,6 +843,15 @@ void draw_randomness(ej_ctx *ctx, const ej_params &p, uint32_t L, uint32_t sigma
                                   ctx->stream));
         // explicit host arrays are pageable: wait before they can change
         sync(ctx);
+    } else if (rd.S <= DRAW_MAX && sig_eff <= 32) {
+        const uint64_t most = std::max((uint64_t)p.r * rd.nw, (uint64_t)p.r * rd.Lpad);
+        hipLaunchKernelGGL(k_draw_all, dim3(p.r + grid_for(ctx, most, 512)), dim3(512),
+                           4 * (size_t)rd.S, ctx->stream, p.seed, p.r, p.z, p.m, L, rd.nw, rd.Lpad,
+                           sig_eff, rd.d_Rwords, rd.d_Rstep, rd.d_pos, rd.d_v, rd.d_spos,
+                           rd.d_sslot, rd.d_J);
+        EJ_CHECK_LAUNCH();
+        rd.Jmax = L;
+        return;
     } else {
         hipLaunchKernelGGL(k_draw_R, dim3(grid_for(ctx, (uint64_t)p.r * rd.nw, 256)), dim3(256), 0,
                            ctx->stream, p.seed, p.r, rd.nw, rd.d_Rwords);

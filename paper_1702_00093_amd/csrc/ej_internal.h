@@ -142,6 +142,7 @@ struct ej_ctx {
     int num_cu = 256;
     int lds_max = 65536;         // max dynamic LDS per workgroup
     uint64_t *pinned = nullptr;  // small pinned host buffer for size read-backs
+    uint8_t *survey = nullptr;   // device, SURVEY_BYTES per CU: a string set's first look
     uint8_t *pinned_out = nullptr;  // grow-only pinned staging of join results
     size_t pinned_out_bytes = 0;
     ej::Timers timers;
@@ -220,6 +221,8 @@ void radix_sort_u64(ej_ctx *ctx, uint64_t *keys_in, uint64_t *keys_out, uint64_t
 
 
 // ------------------------------------------------------------------ stages --
+constexpr uint32_t SURVEY_PARTS = 4;    // workgroups per CU of the first look
+constexpr uint32_t SURVEY_BYTES = 48 * SURVEY_PARTS;
 struct Prep {
     uint32_t n = 0;
     uint64_t base = 0;      // offsets[0]
