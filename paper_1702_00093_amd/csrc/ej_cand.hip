@@ -627,47 +627,131 @@ __global__ void __launch_bounds__(256)
     if (tid == 0) ucount[g] = u;
 }
 
-// Grouping of the raw codes by their top GB bits (GB <= DD_GBITS), not
-// stable: each workgroup counts the groups of its chunk of DD_CHUNK codes in
-// LDS (k_group_count, hist[g * nwg + wg]); after an exclusive scan of the
-// counts it places the low `shift` bits of its codes from LDS cursors
-// (k_group_place).
-constexpr uint32_t DD_GBITS = 11;
-constexpr uint32_t DD_CHUNK = 16384;
+// Grouping of the raw codes by their top GB bits, not stable: each workgroup
+// counts the groups of its chunk of codes in LDS (k_group_count, hist[g * nwg
+// + wg]); after an exclusive scan of the counts it places the low `shift` bits
+// of its codes (k_group_place).  Placing goes through LDS, a tile of DD_TILE
+// codes at a time in group order, so that a wave's stores are a few runs
+// instead of 64 places (36 M 64-bit codes: 462 -> 264 us; 16.8 M 32-bit ones,
+// whose groups are as many, 141 -> 135).
+constexpr uint32_t DD_GBITS = 11;  // 2,048 groups while they hold up to DD_AVG codes each
+constexpr uint32_t DD_GMAX = 12;
+constexpr uint32_t DD_AVG = 6144;
+constexpr uint32_t DD_TILE = 8192;  // 1,024 threads, 8 codes each
+
+// Codes per chunk: few for a small set, which otherwise is a few workgroups'
+// serial work; many for a large one, whose counters are written and scanned.
+inline uint32_t dd_chunk(uint64_t raw) {
+    return raw <= 1u << 20 ? 4096 : raw <= 1u << 24 ? 16384 : 65536;
+}
 
 template <typename C>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
     k_group_count(const C *__restrict__ codes, uint32_t n, const uint64_t *__restrict__ n_dev,
-                  uint32_t shift, uint32_t NG, uint32_t *__restrict__ hist) {
-    __shared__ uint32_t cnt[1u << DD_GBITS];
+                  uint32_t chunk, uint32_t shift, uint32_t NG, uint32_t *__restrict__ hist) {
+    extern __shared__ uint32_t cnt[];  // [NG]
     const uint32_t wg = blockIdx.x, nwg = gridDim.x;
     // a count on the device: past n the buffer holds unwritten entries, so
     // then nothing is grouped (the host sees the count and redoes the join)
     if (n_dev) n = *n_dev > n ? 0u : (uint32_t)*n_dev;
-    for (uint32_t g = threadIdx.x; g < NG; g += 256) cnt[g] = 0;
+    for (uint32_t g = threadIdx.x; g < NG; g += 1024) cnt[g] = 0;
     __syncthreads();
-    const uint32_t b = wg * DD_CHUNK, e = min(n, b + DD_CHUNK);
-    for (uint32_t i = b + threadIdx.x; i < e; i += 256)
-        atomicAdd(&cnt[(uint32_t)(codes[i] >> shift)], 1u);
+    const uint64_t b = (uint64_t)wg * chunk, e = min((uint64_t)n, b + chunk);
+    for (uint64_t i = b + threadIdx.x; i < e; i += 4 * 1024) {
+        C c[4];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++) c[u] = i + 1024 * u < e ? codes[i + 1024 * u] : (C)0;
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++)
+            if (i + 1024 * u < e) atomicAdd(&cnt[(uint32_t)(c[u] >> shift)], 1u);
+    }
     __syncthreads();
-    for (uint32_t g = threadIdx.x; g < NG; g += 256) hist[(uint64_t)g * nwg + wg] = cnt[g];
+    for (uint32_t g = threadIdx.x; g < NG; g += 1024) hist[(uint64_t)g * nwg + wg] = cnt[g];
 }
 
 template <typename C>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
     k_group_place(const C *__restrict__ codes, uint32_t n, const uint64_t *__restrict__ n_dev,
-                  uint32_t shift, uint32_t NG, const uint32_t *__restrict__ offs,
+                  uint32_t chunk, uint32_t shift, uint32_t NG, const uint32_t *__restrict__ offs,
                   uint32_t *__restrict__ out) {
-    __shared__ uint32_t cur[1u << DD_GBITS];
-    const uint32_t wg = blockIdx.x, nwg = gridDim.x;
+    extern __shared__ uint32_t sm[];
+    __shared__ uint32_t wsum[16];
+    uint32_t *cur = sm;                         // [NG] next place of the group's codes
+    uint32_t *cnt = cur + NG;                   // [NG] its codes in the tile, then their start
+    uint32_t *code = cnt + NG;                  // [DD_TILE] the tile in group order
+    uint16_t *grp = (uint16_t *)(code + DD_TILE);  // [DD_TILE] and the groups
+    const uint32_t wg = blockIdx.x, nwg = gridDim.x, tid = threadIdx.x, lane = tid & 63u;
     if (n_dev) n = *n_dev > n ? 0u : (uint32_t)*n_dev;  // as in k_group_count
-    for (uint32_t g = threadIdx.x; g < NG; g += 256) cur[g] = offs[(uint64_t)g * nwg + wg];
+    for (uint32_t g = tid; g < NG; g += 1024) {
+        cur[g] = offs[(uint64_t)g * nwg + wg];
+        cnt[g] = 0;
+    }
     __syncthreads();
-    const uint32_t b = wg * DD_CHUNK, e = min(n, b + DD_CHUNK);
+    const uint64_t b = (uint64_t)wg * chunk, e = min((uint64_t)n, b + chunk);
     const C low = ((C)1 << shift) - 1;
-    for (uint32_t i = b + threadIdx.x; i < e; i += 256) {
-        const C c = codes[i];
-        out[atomicAdd(&cur[(uint32_t)(c >> shift)], 1u)] = (uint32_t)(c & low);
+    const uint32_t per = (NG + 1023) / 1024;  // counters per thread of the scan
+    for (uint64_t t0 = b; t0 < e; t0 += DD_TILE) {
+        C c[8];
+        uint32_t rank[8];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; u++) {
+            const uint64_t i = t0 + u * 1024 + tid;
+            c[u] = i < e ? codes[i] : (C)0;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < 8; u++)
+            if (t0 + u * 1024 + tid < e) rank[u] = atomicAdd(&cnt[(uint32_t)(c[u] >> shift)], 1u);
+        __syncthreads();
+        // the groups' starts in the tile; cur becomes their place less the start
+        uint32_t sum = 0;
+        for (uint32_t q = 0; q < per; q++) {
+            const uint32_t g = tid * per + q;
+            sum += g < NG ? cnt[g] : 0u;
+        }
+        uint32_t incl = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)incl, (unsigned)o, 64);
+            if (lane >= (uint32_t)o) incl += y;
+        }
+        if (lane == 63) wsum[tid >> 6] = incl;
+        __syncthreads();
+        uint32_t at = incl - sum;
+#pragma unroll
+        for (uint32_t w = 0; w < 16; w++) at += w < (tid >> 6) ? wsum[w] : 0u;
+        for (uint32_t q = 0; q < per; q++) {
+            const uint32_t g = tid * per + q;
+            if (g < NG) {
+                const uint32_t k = cnt[g];
+                cnt[g] = at;
+                cur[g] -= at;
+                at += k;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (uint32_t u = 0; u < 8; u++)
+            if (t0 + u * 1024 + tid < e) {
+                const uint32_t g = (uint32_t)(c[u] >> shift), p = cnt[g] + rank[u];
+                code[p] = (uint32_t)(c[u] & low);
+                grp[p] = (uint16_t)g;
+            }
+        __syncthreads();
+        const uint32_t m = (uint32_t)min((uint64_t)DD_TILE, e - t0);
+#pragma unroll
+        for (uint32_t u = 0; u < 8; u++) {
+            const uint32_t i = u * 1024 + tid;
+            if (i < m) out[cur[grp[i]] + i] = code[i];
+        }
+        __syncthreads();
+        // the places after the tile's codes: cur plus the tile's end of the group
+        for (uint32_t q = 0; q < per; q++) {
+            const uint32_t g = tid * per + q;
+            if (g < NG) cur[g] += g + 1 < NG ? cnt[g + 1] : m;
+        }
+        __syncthreads();
+        for (uint32_t g = tid; g < NG; g += 1024) cnt[g] = 0;
+        __syncthreads();
     }
 }
 
@@ -697,6 +781,226 @@ __global__ void k_dedup_out(const uint32_t *__restrict__ ucode, const uint32_t *
         const uint64_t c = ((uint64_t)g << shift) | ucode[(uint64_t)g * DD_UCAP + i];
         out[o + i] = ((c >> B) << 32) | (c & mask);
         if (mult) mult[o + i] = umult[(uint64_t)g * DD_UCAP + i];
+    }
+}
+
+// The same for groups with many distinct codes, and with a lowest count: one
+// workgroup sorts its group's local codes in LDS (stable radix passes of up to
+// 7 bits, ranks by ballot as in the device-wide sort) and keeps one code of
+// every run of at least T equal ones, without its low `drop` bits, once each.
+// The kept codes go to `out` at the group's place, sorted, ucount[g] of them.
+// A group of more codes than LDS takes is sorted in pieces: its codes are
+// counted by their top 10 bits, and each round takes the bins that fit
+// together.  A bin of more than GS_CAP codes sets *overflow.
+//
+// 16 codes per thread, 77 KB of LDS, one workgroup of 16 waves per CU by its
+// registers; bound by its LDS round trips.  36 M codes of 36 bits, 26 M of them
+// distinct, in 4,096 uneven groups (4,000 to 70,000): 1.33 ms, and 0.13 to
+// unpack, for what five passes of the device-wide sort (each reads the codes
+// twice and writes them) and the search for distinct ones did in 2.0; 9.6 M
+// tuple codes of 32 bits, T = 2: 0.20 ms against 1.4.
+constexpr uint32_t GS_ITEMS = 16, GS_WAVES = 16, GS_CAP = 1024 * GS_ITEMS;
+constexpr uint32_t GS_BITS = 7, GS_DIGITS = 1u << GS_BITS;
+constexpr uint32_t GS_BINS = 1024;
+
+__global__ void __launch_bounds__(1024)
+    k_sort_groups(const uint32_t *__restrict__ codes, const uint32_t *__restrict__ gstart,
+                  uint32_t shift, uint32_t T, uint32_t drop, uint32_t *__restrict__ out,
+                  uint32_t *__restrict__ ucount, uint32_t *__restrict__ overflow) {
+    extern __shared__ uint32_t buf[];  // [GS_CAP]
+    __shared__ uint32_t cnt[GS_WAVES * GS_DIGITS];  // [wave][digit]
+    __shared__ uint32_t bins[GS_BINS], wsum[GS_WAVES], taken;
+    const uint32_t g = blockIdx.x, tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+    const uint32_t b = gstart[g], all_m = gstart[g + 1] - b;
+    const uint64_t below = (1ull << lane) - 1ull;
+    // the sum of v over the waves before this one, and over all
+    auto waves_before = [&](uint32_t v, uint32_t &total) {
+        if (lane == 0) wsum[wave] = v;
+        __syncthreads();
+        uint32_t before = 0, all = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < GS_WAVES; w++) {
+            before += w < wave ? wsum[w] : 0u;
+            all += wsum[w];
+        }
+        __syncthreads();
+        total = all;
+        return before;
+    };
+    const uint32_t bshift = shift > 10 ? shift - 10 : 0;
+    const bool whole = all_m <= GS_CAP;
+    if (!whole) {
+        bins[tid] = 0;
+        __syncthreads();
+        for (uint32_t i = tid; i < all_m; i += 1024) atomicAdd(&bins[codes[b + i] >> bshift], 1u);
+        __syncthreads();
+    }
+    uint32_t outn = 0;
+    for (uint32_t bin0 = 0; all_m && bin0 < GS_BINS;) {
+        // the round's bins [bin0, bin1) and codes
+        uint32_t bin1 = GS_BINS, m = all_m;
+        if (!whole) {
+            m = 0;
+            for (bin1 = bin0; bin1 < GS_BINS && m + bins[bin1] <= GS_CAP; bin1++) m += bins[bin1];
+            if (bin1 == bin0) {  // one bin alone is too large
+                if (tid == 0) {
+                    ucount[g] = 0;
+                    atomicOr(overflow, 1u);
+                }
+                return;
+            }
+            if (tid == 0) taken = 0;
+            __syncthreads();
+            for (uint32_t i = tid; i < all_m; i += 1024) {
+                const uint32_t c = codes[b + i], q = c >> bshift;
+                if (q >= bin0 && q < bin1) buf[atomicAdd(&taken, 1u)] = c;
+            }
+            __syncthreads();
+        }
+        bin0 = bin1;
+        // wave w takes codes [w * per, w * per + per), 64 a turn
+        const uint32_t turns = (m + 1023) / 1024, first = wave * turns * 64;
+        uint32_t x[GS_ITEMS];
+#pragma unroll
+        for (uint32_t r = 0; r < GS_ITEMS; r++) {
+            const uint32_t i = first + r * 64 + lane;
+            x[r] = r < turns && i < m ? (whole ? codes[b + i] : buf[i]) : 0u;
+        }
+        const uint32_t passes = (shift + GS_BITS - 1) / GS_BITS;
+        uint32_t at = 0;
+        if (passes == 0) {
+#pragma unroll
+            for (uint32_t r = 0; r < GS_ITEMS; r++) {
+                const uint32_t i = first + r * 64 + lane;
+                if (r < turns && i < m) buf[i] = x[r];
+            }
+            __syncthreads();
+        }
+        for (uint32_t p = 0; p < passes; p++) {
+            const uint32_t bits = (shift - at + passes - p - 1) / (passes - p);
+            const uint32_t mask = (1u << bits) - 1u;
+            uint32_t *mine = cnt + wave * GS_DIGITS;
+            mine[lane] = 0;
+            mine[64 + lane] = 0;
+            uint32_t rank[GS_ITEMS];
+#pragma unroll
+            for (uint32_t r = 0; r < GS_ITEMS; r++) {
+                rank[r] = 0;
+                if (r < turns) {
+                    const bool valid = first + r * 64 + lane < m;
+                    const uint32_t d = (x[r] >> at) & mask;
+                    uint64_t peers = __builtin_amdgcn_ballot_w64(valid);
+                    for (uint32_t k = 0; k < bits; k++) {
+                        const bool bit = (d >> k) & 1u;
+                        const uint64_t bb = __builtin_amdgcn_ballot_w64(bit);
+                        peers &= bit ? bb : ~bb;
+                    }
+                    // LDS operations of one wave keep their order: a turn's reads
+                    // come before the leaders' updates, those before the next reads
+                    const uint32_t before = valid ? mine[d] : 0u;
+                    rank[r] = before + (uint32_t)__popcll(peers & below);
+                    if (valid && (peers & below) == 0)
+                        mine[d] = before + (uint32_t)__popcll(peers);
+                }
+            }
+            __syncthreads();
+            // first positions, by digit, then wave: two counters per thread
+            {
+                const uint32_t q = 2 * tid;
+                uint32_t *c0 = cnt + (q & (GS_WAVES - 1)) * GS_DIGITS + q / GS_WAVES;
+                uint32_t *c1 = c0 + GS_DIGITS;
+                const uint32_t v0 = *c0, v1 = *c1;
+                uint32_t incl = v0 + v1;
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const uint32_t y = (uint32_t)__shfl_up((int)incl, (unsigned)o, 64);
+                    if (lane >= (uint32_t)o) incl += y;
+                }
+                uint32_t total;
+                const uint32_t sum = (uint32_t)__shfl((int)incl, 63, 64);
+                const uint32_t ex = waves_before(sum, total) + incl - v0 - v1;
+                *c0 = ex;
+                *c1 = ex + v0;
+            }
+            __syncthreads();
+#pragma unroll
+            for (uint32_t r = 0; r < GS_ITEMS; r++)
+                if (r < turns && first + r * 64 + lane < m)
+                    buf[mine[(x[r] >> at) & mask] + rank[r]] = x[r];
+            __syncthreads();
+#pragma unroll
+            for (uint32_t r = 0; r < GS_ITEMS; r++) {
+                const uint32_t i = first + r * 64 + lane;
+                if (r < turns && i < m) x[r] = buf[i];
+            }
+            at += bits;
+        }
+        // the first code of every run of at least T
+        uint32_t flags = 0, n = 0;
+#pragma unroll
+        for (uint32_t r = 0; r < GS_ITEMS; r++)
+            if (r < turns) {
+                const uint32_t i = first + r * 64 + lane;
+                bool ok = i < m && (i == 0 || buf[i - 1] != x[r]);
+                if (T > 1) ok = ok && (uint64_t)i + T - 1 < m && buf[i + T - 1] == x[r];
+                flags |= ok ? 1u << r : 0u;
+                n += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(ok));
+            }
+        uint32_t kept;
+        uint32_t pos = waves_before(n, kept);  // (all have read buf by now)
+        uint32_t *to = drop ? buf : out + b + outn;
+#pragma unroll
+        for (uint32_t r = 0; r < GS_ITEMS; r++)
+            if (r < turns) {
+                const bool ok = (flags >> r) & 1u;
+                const uint64_t all = __builtin_amdgcn_ballot_w64(ok);
+                if (ok) to[pos + (uint32_t)__popcll(all & below)] = x[r] >> drop;
+                pos += (uint32_t)__popcll(all);
+            }
+        __syncthreads();
+        if (drop) {
+            // one of each of the shortened codes: not the round before's last one
+            const uint32_t last = outn ? out[b + outn - 1] : 0u;
+            flags = 0;
+            n = 0;
+#pragma unroll
+            for (uint32_t r = 0; r < GS_ITEMS; r++)
+                if (r < turns) {
+                    const uint32_t i = first + r * 64 + lane;
+                    const bool ok =
+                        i < kept && (i ? buf[i - 1] != buf[i] : outn == 0 || last != buf[0]);
+                    flags |= ok ? 1u << r : 0u;
+                    n += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(ok));
+                }
+            pos = outn + waves_before(n, kept);
+#pragma unroll
+            for (uint32_t r = 0; r < GS_ITEMS; r++)
+                if (r < turns) {
+                    const bool ok = (flags >> r) & 1u;
+                    const uint64_t all = __builtin_amdgcn_ballot_w64(ok);
+                    if (ok)
+                        out[b + pos + (uint32_t)__popcll(all & below)] = buf[first + r * 64 + lane];
+                    pos += (uint32_t)__popcll(all);
+                }
+            __syncthreads();
+        }
+        outn += kept;
+    }
+    if (tid == 0) ucount[g] = outn;
+}
+
+// The groups' kept codes (group g's `shift` low bits each, from gstart[g]) at
+// their scanned offsets, unpacked to (a << 32 | b).
+__global__ void k_sorted_out(const uint32_t *__restrict__ codes, const uint32_t *__restrict__ gstart,
+                             const uint32_t *__restrict__ ucount,
+                             const uint32_t *__restrict__ uoff, uint32_t B, uint32_t shift,
+                             uint64_t *__restrict__ out) {
+    const uint32_t g = blockIdx.x, b = gstart[g], o = uoff[g], m = ucount[g];
+    const uint64_t mask = (1ull << B) - 1ull;
+    for (uint32_t i = threadIdx.x; i < m; i += blockDim.x) {
+        const uint64_t c = ((uint64_t)g << shift) | codes[b + i];
+        out[o + i] = ((c >> B) << 32) | (c & mask);
     }
 }
 
@@ -842,6 +1146,79 @@ void bucket_exact(ej_ctx *ctx, const uint64_t *d_keys, const uint32_t *d_perm, u
                        bk.d_gid, bk.d_gstart, (const uint64_t *)d_ng);
     EJ_CHECK_LAUNCH();
     read_back(ctx, d_ng, 8, &bk.ngroups);
+}
+
+// Codes of `bits` bits grouped by their top GB (k_group_count and following):
+// their low `shift` bits in `part`, group g from gstart[g] to gstart[g + 1].
+// With n_dev, *n_dev codes of at most n.
+struct CodeGroups {
+    uint32_t NG, shift;
+    uint32_t *gstart;
+};
+
+template <typename C>
+CodeGroups group_codes(ej_ctx *ctx, const std::string &t, const C *codes, uint32_t n,
+                       const uint64_t *n_dev, uint32_t bits, uint32_t GB, uint32_t *part) {
+    CodeGroups cg{1u << GB, bits - GB, nullptr};
+    const uint32_t chunk = dd_chunk(n), nwg = (uint32_t)(((uint64_t)n + chunk - 1) / chunk);
+    uint32_t *hist = ws<uint32_t>(ctx, t + "_dd_hist", (uint64_t)cg.NG * nwg);
+    cg.gstart = ws<uint32_t>(ctx, t + "_dd_gstart", cg.NG + 1);
+    const size_t place_lds = 8 * (size_t)cg.NG + 6 * DD_TILE;
+    EJ_HIP(hipFuncSetAttribute((const void *)k_group_place<C>,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)place_lds));
+    hipLaunchKernelGGL(k_group_count<C>, dim3(nwg), dim3(1024), 4 * (size_t)cg.NG, ctx->stream,
+                       codes, n, n_dev, chunk, cg.shift, cg.NG, hist);
+    EJ_CHECK_LAUNCH();
+    scan_exclusive_u32(ctx, hist, hist, (uint64_t)cg.NG * nwg, nullptr);
+    hipLaunchKernelGGL(k_group_place<C>, dim3(nwg), dim3(1024), place_lds, ctx->stream, codes, n,
+                       n_dev, chunk, cg.shift, cg.NG, (const uint32_t *)hist, part);
+    EJ_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_group_first, dim3((cg.NG + 256) / 256), dim3(256), 0, ctx->stream,
+                       (const uint32_t *)hist, nwg, cg.NG, n, n_dev, cg.gstart);
+    EJ_CHECK_LAUNCH();
+    return cg;
+}
+
+// Bits of the group for n codes of `bits` bits, 0 if their rest would not fit
+// 31 bits: groups of DD_AVG codes on average, as far as DD_GMAX allows.
+inline uint32_t group_bits(uint64_t n, uint32_t bits) {
+    uint32_t GB = DD_GBITS;
+    while (GB < DD_GMAX && n >> GB > DD_AVG) GB++;
+    GB = std::min(GB, bits);
+    return bits <= GB + 31 ? GB : 0u;
+}
+
+// One code of every run of at least T equal ones, without the low `drop` bits
+// and once each, from the groups' n codes in `part` (k_sort_groups), unpacked;
+// false when a group cannot be sorted in LDS.
+bool sort_groups(ej_ctx *ctx, const std::string &t, const CodeGroups &cg, uint64_t n,
+                 const uint32_t *part, uint32_t T, uint32_t drop, uint32_t B,
+                 uint64_t **d_pairs_out, uint64_t *count) {
+    if (drop > cg.shift) return false;
+    uint32_t *keep = ws<uint32_t>(ctx, t + "_dd_keep", n);
+    uint32_t *ucnt = ws<uint32_t>(ctx, t + "_dd_count", cg.NG);
+    uint32_t *uoff = ws<uint32_t>(ctx, t + "_dd_off", cg.NG);
+    uint64_t *info = ws<uint64_t>(ctx, t + "_dd_info", 2);  // kept codes, overflow
+    EJ_HIP(hipMemsetAsync(info, 0, 16, ctx->stream));
+    const size_t lds = 4 * (size_t)GS_CAP;
+    EJ_HIP(hipFuncSetAttribute((const void *)k_sort_groups,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    hipLaunchKernelGGL(k_sort_groups, dim3(cg.NG), dim3(1024), lds, ctx->stream, part,
+                       (const uint32_t *)cg.gstart, cg.shift, T, drop, keep, ucnt,
+                       (uint32_t *)(info + 1));
+    EJ_CHECK_LAUNCH();
+    scan_exclusive_u32(ctx, ucnt, uoff, cg.NG, info);
+    uint64_t hinfo[2] = {0, 0};
+    read_back(ctx, info, 16, hinfo);
+    if (hinfo[1] != 0) return false;
+    *count = hinfo[0];
+    uint64_t *pairs = ws<uint64_t>(ctx, t + "_pairs", *count);
+    hipLaunchKernelGGL(k_sorted_out, dim3(cg.NG), dim3(256), 0, ctx->stream,
+                       (const uint32_t *)keep, (const uint32_t *)cg.gstart, (const uint32_t *)ucnt,
+                       (const uint32_t *)uoff, B, cg.shift - drop, pairs);
+    EJ_CHECK_LAUNCH();
+    *d_pairs_out = pairs;
+    return true;
 }
 
 // The candidate stage in passes over ranges [lo, hi) of the pairs' smaller
@@ -1033,26 +1410,12 @@ uint64_t candidates(ej_ctx *ctx, const uint64_t *d_keys, const Buckets &bk, cons
     };
     uint64_t cnt = 0;
     // grouped de-duplication while the low 2B - GB bits fit 31 bits
+    const uint32_t GB = group_bits(raw, 2 * B);
     auto grouped = [&](auto *rawbuf, uint32_t *part) -> bool {
-        using C = std::remove_pointer_t<decltype(rawbuf)>;
-        const uint32_t GB = std::min(DD_GBITS, 2 * B);
-        const uint32_t NG = 1u << GB, shift = 2 * B - GB;
-        const uint32_t nwg = (uint32_t)((raw + DD_CHUNK - 1) / DD_CHUNK);
-        uint32_t *ghist = ws<uint32_t>(ctx, t + "_dd_hist", (uint64_t)NG * nwg);
-        uint32_t *gst = ws<uint32_t>(ctx, t + "_dd_gstart", NG + 1);
-        hipLaunchKernelGGL(k_group_count<C>, dim3(nwg), dim3(256), 0, ctx->stream,
-                           (const C *)rawbuf, (uint32_t)raw, (const uint64_t *)nullptr, shift, NG,
-                           ghist);
-        EJ_CHECK_LAUNCH();
-        scan_exclusive_u32(ctx, ghist, ghist, (uint64_t)NG * nwg, nullptr);
-        hipLaunchKernelGGL(k_group_place<C>, dim3(nwg), dim3(256), 0, ctx->stream,
-                           (const C *)rawbuf, (uint32_t)raw, (const uint64_t *)nullptr, shift, NG,
-                           (const uint32_t *)ghist, part);
-        EJ_CHECK_LAUNCH();
-        hipLaunchKernelGGL(k_group_first, dim3((NG + 256) / 256), dim3(256), 0, ctx->stream,
-                           (const uint32_t *)ghist, nwg, NG, (uint32_t)raw,
-                           (const uint64_t *)nullptr, gst);
-        EJ_CHECK_LAUNCH();
+        const CodeGroups cg =
+            group_codes(ctx, t, (const std::remove_pointer_t<decltype(rawbuf)> *)rawbuf,
+                        (uint32_t)raw, nullptr, 2 * B, GB, part);
+        const uint32_t NG = cg.NG, shift = cg.shift, *gst = cg.gstart;
         uint32_t *ucode = ws<uint32_t>(ctx, t + "_dd_code", (uint64_t)NG * DD_UCAP);
         uint32_t *umult = ws<uint32_t>(ctx, t + "_dd_mult", (uint64_t)NG * DD_UCAP);
         uint32_t *ucnt = ws<uint32_t>(ctx, t + "_dd_count", NG);
@@ -1060,13 +1423,14 @@ uint64_t candidates(ej_ctx *ctx, const uint64_t *d_keys, const Buckets &bk, cons
         uint64_t *info = ws<uint64_t>(ctx, t + "_dd_info", 2);  // distinct codes, overflow
         EJ_HIP(hipMemsetAsync(info, 0, 16, ctx->stream));
         hipLaunchKernelGGL(k_dedup_groups, dim3(NG), dim3(256), 0, ctx->stream,
-                           (const uint32_t *)part, (const uint32_t *)gst, ucode, umult, ucnt,
+                           (const uint32_t *)part, gst, ucode, umult, ucnt,
                            (uint32_t *)(info + 1));
         EJ_CHECK_LAUNCH();
         scan_exclusive_u32(ctx, ucnt, uoff, NG, info);
         uint64_t hinfo[2] = {0, 0};
         read_back(ctx, info, 16, hinfo);
-        if (hinfo[1] != 0) return false;
+        if (hinfo[1] != 0)  // a group of too many distinct codes: sorted in LDS, if it fits
+            return !d_order_out && sort_groups(ctx, t, cg, raw, part, 1, 0, B, d_pairs_out, &cnt);
         cnt = hinfo[0];
         uint64_t *pairs = ws<uint64_t>(ctx, t + "_pairs", cnt);
         uint32_t *mult = d_order_out ? ws<uint32_t>(ctx, t + "_mult", cnt) : nullptr;
@@ -1085,7 +1449,7 @@ uint64_t candidates(ej_ctx *ctx, const uint64_t *d_keys, const Buckets &bk, cons
         }
         return true;
     };
-    const bool fits_grouped = 2 * B <= DD_GBITS + 31 && ctx->tune.dedup_sort == 0;
+    const bool fits_grouped = GB != 0 && ctx->tune.dedup_sort == 0;
     if (2 * B <= 32) {
         // 32-bit codes (both indexes below 2^16)
         uint32_t *raw32 = ws<uint32_t>(ctx, t + "_raw32", raw);
@@ -1215,23 +1579,13 @@ void candidates_dev(ej_ctx *ctx, const uint64_t *d_keys, const Buckets &bk,
     if (2 * B > DD_GBITS + 31) fail(EJ_EUNSUPPORTED, "candidates_dev: codes too wide to group");
     const uint32_t GB = std::min(DD_GBITS, 2 * B);
     const uint32_t NG = 1u << GB, shift = 2 * B - GB;
-    const uint32_t nwd = (uint32_t)((raw_cap + DD_CHUNK - 1) / DD_CHUNK);
-    uint32_t *ghist = ws<uint32_t>(ctx, t + "_dd_hist", (uint64_t)NG * nwd);
-    uint32_t *gst = ws<uint32_t>(ctx, t + "_dd_gstart", NG + 1);
+    CodeGroups cg{};
     auto group = [&](auto *rawbuf, uint32_t *part) {
-        using C = std::remove_pointer_t<decltype(rawbuf)>;
         pw_emit(ctx, pw, (const uint32_t *)bk.d_dk, (const uint64_t *)key_s,
                 (const uint32_t *)len_s, (const uint32_t *)bk.d_ids, n, (uint32_t)tot, K,
                 PairCoder{B}, rawbuf, raw_cap);
-        hipLaunchKernelGGL(k_group_count<C>, dim3(nwd), dim3(256), 0, ctx->stream,
-                           (const C *)rawbuf, (uint32_t)raw_cap, (const uint64_t *)cnt_dev, shift,
-                           NG, ghist);
-        EJ_CHECK_LAUNCH();
-        scan_exclusive_u32(ctx, ghist, ghist, (uint64_t)NG * nwd, nullptr);
-        hipLaunchKernelGGL(k_group_place<C>, dim3(nwd), dim3(256), 0, ctx->stream,
-                           (const C *)rawbuf, (uint32_t)raw_cap, (const uint64_t *)cnt_dev, shift,
-                           NG, (const uint32_t *)ghist, part);
-        EJ_CHECK_LAUNCH();
+        cg = group_codes(ctx, t, (const std::remove_pointer_t<decltype(rawbuf)> *)rawbuf,
+                         (uint32_t)raw_cap, (const uint64_t *)cnt_dev, 2 * B, GB, part);
     };
     uint32_t *part = nullptr;
     if (2 * B <= 32) {
@@ -1243,16 +1597,13 @@ void candidates_dev(ej_ctx *ctx, const uint64_t *d_keys, const Buckets &bk,
         part = (uint32_t *)ws<uint64_t>(ctx, t + "_raw_sorted", raw_cap);
         group(raw64, part);
     }
-    hipLaunchKernelGGL(k_group_first, dim3((NG + 256) / 256), dim3(256), 0, ctx->stream,
-                       (const uint32_t *)ghist, nwd, NG, (uint32_t)raw_cap,
-                       (const uint64_t *)cnt_dev, gst);
-    EJ_CHECK_LAUNCH();
     uint32_t *ucode = ws<uint32_t>(ctx, t + "_dd_code", (uint64_t)NG * DD_UCAP);
     uint32_t *umult = ws<uint32_t>(ctx, t + "_dd_mult", (uint64_t)NG * DD_UCAP);
     uint32_t *ucnt = ws<uint32_t>(ctx, t + "_dd_count", NG);
     uint32_t *uoff = ws<uint32_t>(ctx, t + "_dd_off", NG);
     hipLaunchKernelGGL(k_dedup_groups, dim3(NG), dim3(256), 0, ctx->stream, (const uint32_t *)part,
-                       (const uint32_t *)gst, ucode, umult, ucnt, (uint32_t *)(cnt_dev + 2));
+                       (const uint32_t *)cg.gstart, ucode, umult, ucnt,
+                       (uint32_t *)(cnt_dev + 2));
     EJ_CHECK_LAUNCH();
     scan_exclusive_u32(ctx, ucnt, uoff, NG, cnt_dev + 1);
     uint64_t *pairs = ws<uint64_t>(ctx, t + "_pairs", cnt_cap);
@@ -1317,6 +1668,15 @@ uint64_t candidates_plus(ej_ctx *ctx, const uint64_t *d_keys, const Buckets &bk,
     uint64_t *sorted = ws<uint64_t>(ctx, t + "_tuples_sorted", raw);
     pw_emit(ctx, pw, (const uint32_t *)bk.d_dk, (const uint64_t *)key_s, (const uint32_t *)len_s,
             (const uint32_t *)bk.d_ids, ne, (uint32_t)tot, K, coder, tup, raw);
+    const uint32_t GB = group_bits(raw, 2 * B + 2 * KB);
+    if (GB && ctx->tune.dedup_sort == 0) {
+        const CodeGroups cg = group_codes(ctx, t, (const uint64_t *)tup, (uint32_t)raw, nullptr,
+                                          2 * B + 2 * KB, GB, (uint32_t *)sorted);
+        uint64_t cnt = 0;
+        if (sort_groups(ctx, t, cg, raw, (uint32_t *)sorted, T, 2 * KB, B, d_pairs_out, &cnt))
+            return cnt;
+    }
+    // (the tuples are intact, the grouping wrote to `sorted`)
     radix_sort_u64(ctx, tup, sorted, raw, 2 * B + 2 * KB, ctx->tune.radix_bits);
     uint32_t *flags = ws<uint32_t>(ctx, t + "_tflags", raw);
     uint32_t *pos = ws<uint32_t>(ctx, t + "_tpos", raw);
