@@ -527,6 +527,9 @@ uint64_t ej_query_workspace_estimate(const ej_index *index, const uint64_t *q_of
 void ej_index_set_hbm_limit(ej_index *index, uint64_t bytes);
 uint32_t ej_index_size(const ej_index *index);
 void ej_qresult_free(ej_qresult *res);
+/* The context may keep the memory of one freed index (at most a 64th of the
+ * device's) for the next index built or grown on it; it is freed with the
+ * context, or when an allocation of the library would fail without it. */
 void ej_index_free(ej_index *index);
 
 #ifdef __cplusplus

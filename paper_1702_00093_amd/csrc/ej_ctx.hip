@@ -85,6 +85,7 @@ void *ws_get(ej_ctx *ctx, const std::string &name, size_t bytes) {
         }
         size_t want = bytes + bytes / 8 + 256;  // grow with headroom
         hipError_t e = hipMalloc(&b.p, want);
+        if (e == hipErrorOutOfMemory && spare_release(ctx)) e = hipMalloc(&b.p, want);
         if (e != hipSuccess) {
             b.p = nullptr;
             fail(EJ_ENOMEM, "device allocation of " + std::to_string(want) + " bytes for '" +
@@ -93,6 +94,55 @@ void *ws_get(ej_ctx *ctx, const std::string &name, size_t bytes) {
         b.bytes = want;
     }
     return b.p;
+}
+
+void *slab_take(ej_ctx *ctx, size_t bytes, size_t *got) {
+    {
+        std::lock_guard<std::mutex> hold(ctx->spare_lock);
+        if (ctx->spare && ctx->spare_bytes >= bytes && ctx->spare_bytes / 2 <= bytes) {
+            void *p = ctx->spare;
+            *got = ctx->spare_bytes;
+            ctx->spare = nullptr;
+            ctx->spare_bytes = 0;
+            return p;
+        }
+    }
+    void *p = nullptr;
+    hipError_t e = hipMalloc(&p, bytes);
+    if (e == hipErrorOutOfMemory && spare_release(ctx)) e = hipMalloc(&p, bytes);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        fail(EJ_ENOMEM, "index allocation of " + std::to_string(bytes) + " bytes failed");
+    }
+    *got = bytes;
+    return p;
+}
+
+void slab_give(ej_ctx *ctx, void *p, size_t bytes) {
+    if (!p) return;
+    {
+        std::lock_guard<std::mutex> hold(ctx->spare_lock);
+        if (bytes <= ctx->spare_max && bytes > ctx->spare_bytes) {
+            std::swap(p, ctx->spare);
+            ctx->spare_bytes = bytes;
+        }
+    }
+    if (p) (void)hipFree(p);
+}
+
+bool spare_release(ej_ctx *ctx) {
+    void *p;
+    {
+        std::lock_guard<std::mutex> hold(ctx->spare_lock);
+        p = ctx->spare;
+        ctx->spare = nullptr;
+        ctx->spare_bytes = 0;
+    }
+    if (p) {
+        (void)hipGetLastError();
+        (void)hipFree(p);
+    }
+    return p != nullptr;
 }
 
 size_t ws_capacity(ej_ctx *ctx, const std::string &name) {
@@ -175,6 +225,9 @@ ej_status ej_create(ej_ctx **out, int device, void *hip_stream) {
         EJ_HIP(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device));
         ctx->lds_max = lds;
         EJ_HIP(hipHostMalloc((void **)&ctx->pinned, 4096, hipHostMallocDefault));
+        size_t free_bytes = 0, all_bytes = 0;
+        EJ_HIP(hipMemGetInfo(&free_bytes, &all_bytes));
+        ctx->spare_max = all_bytes / 64;
         EJ_HIP(hipMalloc((void **)&ctx->survey, (size_t)ctx->num_cu * SURVEY_BYTES));
         static_scratch_init(device);
         for (int i = 0; i < 8; i++) EJ_HIP(hipEventCreate(&ctx->timers.ev[i]));
@@ -203,6 +256,7 @@ void ej_destroy(ej_ctx *ctx) {
     ctx->graphs.clear();
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     if (ctx->survey) (void)hipFree(ctx->survey);
+    (void)spare_release(ctx);
     if (ctx->pinned_out) (void)hipHostFree(ctx->pinned_out);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;

@@ -37,6 +37,9 @@ struct ej_index {
     uint32_t *d_planes = nullptr;  // bit planes of their codes (verification)
     Rand rd;                       // random streams (owned copies)
     std::vector<void *> owned;
+    // the arrays that grow with the strings (codes, offsets, tables, planes)
+    void *slab = nullptr;
+    size_t slab_bytes = 0;
 };
 
 namespace {
@@ -49,11 +52,45 @@ inline uint32_t grid_for(ej_ctx *ctx, uint64_t work, uint32_t block) {
     return (uint32_t)g;
 }
 
+// The arrays of an index of n strings with `total` characters and tot table
+// entries, in one slab.
+struct SlabParts {
+    uint8_t *codes;
+    uint64_t *offsets, *key_s;
+    uint32_t *dk, *len_s, *ids, *planes;
+};
+
+SlabParts slab_parts(ej_ctx *ctx, uint64_t n, uint64_t total, uint64_t tot, uint32_t sigma,
+                     void **slab, size_t *bytes) {
+    size_t at = 0;
+    auto part = [&](uint64_t b) {
+        const size_t o = at;
+        at += (b + 255) & ~(uint64_t)255;
+        return o;
+    };
+    const size_t codes = part(total + 64), offsets = part(8 * (n + 1)), key_s = part(8 * tot),
+                 dk = part(4 * tot), len_s = part(4 * tot), ids = part(4 * tot),
+                 planes = part(4 * plane_words(total) * plane_count(sigma));
+    char *p = (char *)slab_take(ctx, at, bytes);
+    *slab = p;
+    return SlabParts{(uint8_t *)(p + codes),    (uint64_t *)(p + offsets),
+                     (uint64_t *)(p + key_s),   (uint32_t *)(p + dk),
+                     (uint32_t *)(p + len_s),   (uint32_t *)(p + ids),
+                     (uint32_t *)(p + planes)};
+}
+
+template <typename T>
+void copy_on(ej_ctx *ctx, T *dst, const T *src, uint64_t count) {
+    if (count)
+        EJ_HIP(hipMemcpyAsync(dst, src, count * sizeof(T), hipMemcpyDeviceToDevice, ctx->stream));
+}
+
 template <typename T>
 T *own_copy(ej_index *ix, const T *src, size_t count) {
     T *dst = nullptr;
     size_t bytes = std::max<size_t>(count * sizeof(T), 16);
     hipError_t e = hipMalloc((void **)&dst, bytes);
+    if (e == hipErrorOutOfMemory && spare_release(ix->ctx)) e = hipMalloc((void **)&dst, bytes);
     if (e != hipSuccess) fail(EJ_ENOMEM, "index allocation failed");
     ix->owned.push_back(dst);
     if (src && count)
@@ -402,9 +439,13 @@ ej_status ej_index_build(ej_ctx *ctx, const uint8_t *strings, const uint64_t *of
         Buckets bk;
         bucket(ctx, keys, pp.d_len, pp.d_perm, n, ix->T, 32, bk, "ix");
         // owned copies
-        ix->d_codes = own_copy(ix, pp.d_codes, pp.total + 64);
+        const SlabParts parts = slab_parts(ctx, n, pp.total, tot, pp.sigma, &ix->slab,
+                                           &ix->slab_bytes);
+        ix->d_codes = parts.codes;
+        copy_on(ctx, ix->d_codes, (const uint8_t *)pp.d_codes, pp.total + 64);
         // offsets rebased onto the owned code array
-        ix->d_offsets = own_copy(ix, d_off, (uint64_t)n + 1);
+        ix->d_offsets = parts.offsets;
+        copy_on(ctx, ix->d_offsets, d_off, (uint64_t)n + 1);
         ix->rd = rd;
         ix->rd.d_Rwords = own_copy(ix, rd.d_Rwords, (size_t)rd.r * rd.nw);
         ix->rd.d_Rstep = own_copy(ix, rd.d_Rstep, (size_t)rd.r * rd.Lpad);
@@ -413,10 +454,11 @@ ej_status ej_index_build(ej_ctx *ctx, const uint8_t *strings, const uint64_t *of
         ix->rd.d_spos = own_copy(ix, rd.d_spos, (size_t)ix->T * rd.m);
         ix->rd.d_sslot = own_copy(ix, rd.d_sslot, (size_t)ix->T * rd.m);
         ix->rd.d_J = own_copy(ix, rd.d_J, (size_t)rd.r);
-        ix->d_ids = own_copy(ix, bk.d_ids, tot);
-        ix->d_dk = own_copy<uint32_t>(ix, nullptr, tot);
-        ix->d_key_s = own_copy<uint64_t>(ix, nullptr, tot);
-        ix->d_len_s = own_copy<uint32_t>(ix, nullptr, tot);
+        ix->d_ids = parts.ids;
+        copy_on(ctx, ix->d_ids, (const uint32_t *)bk.d_ids, tot);
+        ix->d_dk = parts.dk;
+        ix->d_key_s = parts.key_s;
+        ix->d_len_s = parts.len_s;
         if (tot)
             hipLaunchKernelGGL(k_sorted_attrs_full, dim3(grid_for(ctx, tot, 256)), dim3(256), 0,
                                ctx->stream, (const uint64_t *)keys, (const uint32_t *)ix->d_ids,
@@ -426,8 +468,7 @@ ej_status ej_index_build(ej_ctx *ctx, const uint8_t *strings, const uint64_t *of
         // what verification needs of the index strings, kept for every query
         // batch: the bit planes (the match masks of the other forms, five
         // times their size, follow when a batch first asks for such a form)
-        ix->d_planes =
-            own_copy<uint32_t>(ix, nullptr, plane_words(pp.total) * plane_count(pp.sigma));
+        ix->d_planes = parts.planes;
         build_planes(ctx, pp.d_codes, pp.total, pp.sigma, ix->d_planes);
         // the owned offsets must be relative to the owned codes: base 0
         if (pp.base) {
@@ -454,6 +495,8 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
     if (!ix || !offsets) return EJ_EINVAL;
     ej_ctx *ctx = ix->ctx;
     std::vector<void *> fresh;  // allocations of this call, released on failure
+    void *slab = nullptr;
+    size_t slab_bytes = 0;
     ej_status st = run_guarded(ctx, [&] {
         if (n_new == 0) return;
         if ((uint64_t)ix->n + n_new >= 0x80000000ull) fail(EJ_EINVAL, "n must stay below 2^31");
@@ -502,7 +545,10 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         // until every allocation has succeeded)
         auto alloc = [&](size_t bytes) -> void * {
             void *p = nullptr;
-            if (hipMalloc(&p, std::max<size_t>(bytes, 16)) != hipSuccess) {
+            hipError_t e = hipMalloc(&p, std::max<size_t>(bytes, 16));
+            if (e == hipErrorOutOfMemory && spare_release(ctx))
+                e = hipMalloc(&p, std::max<size_t>(bytes, 16));
+            if (e != hipSuccess) {
                 (void)hipGetLastError();
                 fail(EJ_ENOMEM, "index insert: device allocation failed");
             }
@@ -511,12 +557,10 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         };
         const uint64_t totN = (uint64_t)T * nN;
         const uint64_t charsN = ix->total + pq.total;
-        uint32_t *dk = (uint32_t *)alloc(4 * totN);
-        uint64_t *key = (uint64_t *)alloc(8 * totN);
-        uint32_t *len = (uint32_t *)alloc(4 * totN);
-        uint32_t *id = (uint32_t *)alloc(4 * totN);
-        uint8_t *codes = (uint8_t *)alloc(charsN + 64);
-        uint64_t *offs = (uint64_t *)alloc(8 * (nN + 1));
+        const SlabParts parts = slab_parts(ctx, nN, charsN, totN, ix->sigma, &slab, &slab_bytes);
+        uint32_t *dk = parts.dk, *len = parts.len_s, *id = parts.ids, *planes = parts.planes;
+        uint64_t *key = parts.key_s, *offs = parts.offsets;
+        uint8_t *codes = parts.codes;
         const bool masked = ix->masks.words != nullptr;  // a batch has asked for them
         uint32_t *mw = nullptr;
         uint64_t *mo = nullptr;
@@ -524,8 +568,6 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
             mw = (uint32_t *)alloc(4 * mask_words_bound(charsN, (uint32_t)nN, ix->sigma));
             mo = (uint64_t *)alloc(8 * (nN + 1));
         }
-        uint32_t *planes =
-            (uint32_t *)alloc(4 * plane_words(charsN) * plane_count(ix->sigma));
         hipLaunchKernelGGL(k_merge_tables, dim3(grid_for(ctx, totN, 256)), dim3(256), 0,
                            ctx->stream, (const uint32_t *)ix->d_dk, (const uint64_t *)ix->d_key_s,
                            (const uint32_t *)ix->d_len_s, (const uint32_t *)ix->d_ids, ix->n,
@@ -552,8 +594,7 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         build_planes(ctx, codes, charsN, ix->sigma, planes);
         sync(ctx);
         // swap in the grown arrays; release the replaced ones
-        void *old[] = {ix->d_dk, ix->d_key_s, ix->d_len_s, ix->d_ids, ix->d_codes, ix->d_offsets,
-                       (void *)ix->masks.words, (void *)ix->masks.off, ix->d_planes};
+        void *old[] = {(void *)ix->masks.words, (void *)ix->masks.off};
         for (void *p : old) {
             auto it = std::find(ix->owned.begin(), ix->owned.end(), p);
             if (it != ix->owned.end()) ix->owned.erase(it);
@@ -561,6 +602,8 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         }
         ix->owned.insert(ix->owned.end(), fresh.begin(), fresh.end());
         fresh.clear();
+        std::swap(ix->slab, slab);
+        std::swap(ix->slab_bytes, slab_bytes);
         ix->d_dk = dk;
         ix->d_key_s = key;
         ix->d_len_s = len;
@@ -573,6 +616,8 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         ix->total = charsN;
         ix->maxlen = std::max(ix->maxlen, pq.maxlen);
     });
+    if (slab && st != EJ_OK) (void)hipStreamSynchronize(ctx->stream);
+    slab_give(ctx, slab, slab_bytes);  // the replaced one, or this call's on failure
     for (void *p : fresh) (void)hipFree(p);
     return st;
 }
@@ -605,13 +650,17 @@ ej_status ej_query_batch(ej_index *ix, const uint8_t *q, const uint64_t *q_offse
         // admission by free HBM (or the configured limit)
         size_t freeb = 0, totalb = 0;
         EJ_HIP(hipMemGetInfo(&freeb, &totalb));
-        const uint64_t avail = ix->hbm_limit ? ix->hbm_limit : (uint64_t)freeb;
+        uint64_t avail = ix->hbm_limit ? ix->hbm_limit : (uint64_t)freeb;
         uint32_t Kmax = 0;
         for (uint32_t i = 0; i < nq; i++) Kmax = std::max(Kmax, Kq[i]);
         // admission, checked again as each data-dependent size becomes known
         // and before any of that stage's memory is requested
         uint64_t need = estimate(ix, qtotal, nq);
         auto admit = [&](const char *what) {
+            if (need > avail && !ix->hbm_limit && spare_release(ctx)) {
+                EJ_HIP(hipMemGetInfo(&freeb, &totalb));
+                avail = freeb;
+            }
             if (need > avail)
                 fail(EJ_ENOMEM, std::string("batch needs ~") + std::to_string(need) +
                                     " bytes (" + what + "), " + std::to_string(avail) +
@@ -778,6 +827,7 @@ void ej_index_free(ej_index *ix) {
         (void)hipSetDevice(ix->ctx->device);
         (void)hipStreamSynchronize(ix->ctx->stream);
     }
+    if (ix->ctx) slab_give(ix->ctx, ix->slab, ix->slab_bytes);
     for (void *p : ix->owned) (void)hipFree(p);
     delete ix;
 }

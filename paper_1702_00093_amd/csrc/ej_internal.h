@@ -8,6 +8,7 @@
 #include <functional>
 #include <new>
 #include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -142,6 +143,10 @@ struct ej_ctx {
     int num_cu = 256;
     int lds_max = 65536;         // max dynamic LDS per workgroup
     uint64_t *pinned = nullptr;  // small pinned host buffer for size read-backs
+    // The memory of an index freed last, for the next one (slab_take).
+    std::mutex spare_lock;
+    void *spare = nullptr;
+    size_t spare_bytes = 0, spare_max = 0;
     uint8_t *survey = nullptr;   // device, SURVEY_BYTES per CU: a string set's first look
     uint8_t *pinned_out = nullptr;  // grow-only pinned staging of join results
     size_t pinned_out_bytes = 0;
@@ -187,6 +192,18 @@ void sync(ej_ctx *ctx);
 // memset) directly, or, with the context's graph mode on, as a captured graph
 // cached under `key`, which must identify every argument of the launches.
 void run_captured(ej_ctx *ctx, const std::string &key, const std::function<void()> &enqueue);
+// Memory of an index, in one piece.  slab_give keeps the piece in the context
+// when it is within spare_max (a 64th of the device's memory) and larger than
+// the one kept so far, and slab_take hands it out again for a need of at least
+// half its size; otherwise they allocate and free.  Allocating and freeing an
+// index in sixteen pieces took from 1.6 ms to 15 ms, depending on what else the
+// process had allocated.  The kept piece is freed with the context, and before
+// any allocation of the library fails for lack of memory (spare_release).
+// Callers have waited for the work on the piece.
+void *slab_take(ej_ctx *ctx, size_t bytes, size_t *got);
+void slab_give(ej_ctx *ctx, void *p, size_t bytes);
+bool spare_release(ej_ctx *ctx);  // whether there was one
+
 // Copies `count` u64 words from device to host through the pinned buffer.
 void read_back(ej_ctx *ctx, const void *dsrc, size_t bytes, void *hdst);
 

@@ -74,3 +74,38 @@ def test_codes_above_32_bits(ej):
         assert np.array_equal(part.dist, whole.dist[lo:hi])
         assert np.array_equal(part.offsets + lo, whole.offsets[a:a + 1001])
     ix.close()
+
+
+def test_index_memory_is_reused(ej, oracle_lib):
+    """Indexes of other sizes built in the memory of freed ones, one grown by an
+    insert, two alive at a time: every one answers as the oracle does."""
+    ctx = ej.Context(0)
+    r, z, m, L = 3, 4, 4, 32
+    held = []
+    for i, (bases, letters) in enumerate([(60, b"ACGT"), (50, b"ACGT"), (58, sd.DNA), (9, b"ACGT"),
+                                          (60, bytes(range(65, 85))), (61, b"ACGT")]):
+        col = sd.clusters(30 + i, bases, lambda rr, b: 4, lambda rr: rr.integers(60, 200),
+                          lambda rr, LL: rr.poisson(3), letters=letters)
+        Kq = np.full(20, 8, np.uint32)
+        q, qo = col.chars[:int(col.offsets[20])], col.offsets[:21]
+        print(f"[gpu-case] index memory {i} n={col.n}", flush=True)
+        ix = ej.Index(ctx, col.chars, col.offsets, r, z, m, seed=i, L=L)
+        ref = oracle_lib.query(col.chars, col.offsets, q, qo, Kq, r, z, m, seed=i, L=L)
+        if i % 2:
+            ix.insert(col.chars, col.offsets)  # (queries below find both copies)
+        held.append((ix, q, qo, Kq, ref, i % 2, col.n))
+        if len(held) > 2:
+            held.pop(0)[0].close()
+        for jx, jq, jqo, jK, (ro, ri, rd), twice, n in held:
+            res = jx.query(jq, jqo, jK)
+            if twice:
+                for k in range(len(jqo) - 1):
+                    got = res.ids[int(res.offsets[k]):int(res.offsets[k + 1])]
+                    want = ri[int(ro[k]):int(ro[k + 1])]
+                    assert sorted(got.tolist()) == sorted([*want, *(want.astype(np.int64) + n)])
+            else:
+                assert res.offsets.astype(np.uint64).tolist() == ro.tolist()
+                assert res.ids.astype(np.uint32).tolist() == ri.tolist()
+                assert res.dist.astype(np.int64).tolist() == rd.astype(np.int64).tolist()
+    for jx, *_ in held:
+        jx.close()
