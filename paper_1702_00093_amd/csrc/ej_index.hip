@@ -435,9 +435,11 @@ ej_status ej_index_build(ej_ctx *ctx, const uint8_t *strings, const uint64_t *of
         draw_randomness(ctx, *p, pp.L, pp.sigma, rd, "ix");
         const uint64_t tot = (uint64_t)ix->T * n;
         uint64_t *keys = ws<uint64_t>(ctx, "ix_keys", tot);
-        embed_keys(ctx, pp, rd, keys, nullptr);
+        uint32_t *bdk = nullptr, *bids = nullptr;
+        bucket_inputs(ctx, tot, "ix", &bdk, &bids);
+        embed_keys(ctx, pp, rd, keys, nullptr, bdk, bids, 61u - 32u);
         Buckets bk;
-        bucket(ctx, keys, pp.d_len, pp.d_perm, n, ix->T, 32, bk, "ix");
+        bucket(ctx, keys, pp.d_len, pp.d_perm, n, ix->T, 32, bk, "ix", false, true, false);
         // owned copies
         const SlabParts parts = slab_parts(ctx, n, pp.total, tot, pp.sigma, &ix->slab,
                                            &ix->slab_bytes);
@@ -528,9 +530,11 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         const uint32_t T = ix->T;
         const uint64_t totB = (uint64_t)T * n_new;
         uint64_t *keys = ws<uint64_t>(ctx, "ii_keys", totB);
-        embed_keys(ctx, pq, ix->rd, keys, nullptr);
+        uint32_t *bdk = nullptr, *bids = nullptr;
+        bucket_inputs(ctx, totB, "ii", &bdk, &bids);
+        embed_keys(ctx, pq, ix->rd, keys, nullptr, bdk, bids, 61u - 32u);
         Buckets bk;
-        bucket(ctx, keys, pq.d_len, pq.d_perm, n_new, T, 32, bk, "ii");
+        bucket(ctx, keys, pq.d_len, pq.d_perm, n_new, T, 32, bk, "ii", false, true, false);
         uint32_t *dkB = ws<uint32_t>(ctx, "ii_dkB", totB);
         uint64_t *keyB = ws<uint64_t>(ctx, "ii_keyB", totB);
         uint32_t *lenB = ws<uint32_t>(ctx, "ii_lenB", totB);
