@@ -449,12 +449,65 @@ __global__ void __launch_bounds__(512)
 
 // --------------------------------------------------------------- the walk --
 
+// The z keys of a walk from its recorded symbols, and where they go.
+//      key = sum_k u_k v_k mod 2^61-1, u_k = symbol + 1 <= 256.
+//      v_k is split into four 16-bit limbs (wave-uniform, scalar); each
+//      limb sum sum_k u_k * limb is exact in 32 bits for m <= 64
+//      (64 * 257 * 2^16 < 2^31), one full-rate 24-bit multiply-add per
+//      limb and sample; the limbs recombine once per key.
+struct KeysOut {
+    uint64_t *keys;
+    uint8_t *sig;
+    uint32_t *dk, *ids;
+    uint32_t dk_shift, n, at, rank, id;
+};
+
+template <bool REC>
+__device__ __forceinline__ void form_keys(const uint8_t *sig, const uint8_t *rec,
+                                          const uint32_t *__restrict__ pos,
+                                          const uint64_t *__restrict__ v, uint32_t l, uint32_t row,
+                                          uint32_t r, uint32_t z, uint32_t m, uint32_t lane,
+                                          const KeysOut &o) {
+    const uint32_t S = z * m;
+    for (uint32_t t = 0; t < z; t++) {
+        const uint64_t *vt = v + ((size_t)l * z + t) * m;
+        uint32_t s0 = 0, s1 = 0, s2 = 0, s3 = 0;
+        const uint32_t *pt = pos + (size_t)row * S + t * m;
+        for (uint32_t kk = 0; kk < m; kk++) {
+            const uint32_t u =
+                (uint32_t)(REC ? rec[pt[kk]] : sig[(t * m + kk) * 64 + lane]) + 1u;
+            const uint64_t vv = vt[kk];
+            s0 += __umul24(u, (uint32_t)vv & 0xFFFFu);
+            s1 += __umul24(u, (uint32_t)(vv >> 16) & 0xFFFFu);
+            s2 += __umul24(u, (uint32_t)(vv >> 32) & 0xFFFFu);
+            s3 += __umul24(u, (uint32_t)(vv >> 48));
+        }
+        // s0 + s1 2^16 + s2 2^32 + s3 2^48 < 2^80, reduced with 2^61 == 1 (mod P)
+        const unsigned __int128 x = (unsigned __int128)s0 + ((unsigned __int128)s1 << 16) +
+                                    ((unsigned __int128)s2 << 32) + ((unsigned __int128)s3 << 48);
+        uint64_t res = (uint64_t)(x & P61) + (uint64_t)(x >> 61);
+        res = (res & P61) + (res >> 61);
+        if (res >= P61) res -= P61;
+        o.keys[((size_t)l * z + t) * o.n + o.at] = res;
+        if (o.dk) {
+            o.dk[((size_t)l * z + t) * o.n + o.rank] = (uint32_t)(res >> o.dk_shift);
+            o.ids[((size_t)l * z + t) * o.n + o.rank] = o.at;
+        }
+        if (o.sig) {
+            uint8_t *dst = o.sig + (((size_t)o.id * r + l) * z + t) * m;
+            for (uint32_t kk = 0; kk < m; kk++)
+                dst[kk] = REC ? rec[pt[kk]] : sig[(t * m + kk) * 64 + lane];
+        }
+    }
+}
+
 // REC = true (walks of at most EMBED_REC_STEPS steps): every step's symbol
 // is recorded in LDS (Lb bytes per lane) and the samples are read from the
 // record through the sample positions when the keys are formed, so the walk
 // itself never looks at the sample list.  REC = false: the walk stores each
 // sampled symbol as it passes the sample's step (the positions sorted, one
-// scalar read per sample).
+// scalar read per sample); alphabets of more than 32 letters (k_walk takes the
+// others).
 template <int BW, bool RSTEP, bool REC>
 __global__ void __launch_bounds__(64)
     k_embed(const uint32_t *__restrict__ packed, const uint64_t *__restrict__ offsets,
@@ -600,44 +653,221 @@ __global__ void __launch_bounds__(64)
         }
     }
 
-    // ---- two-level hash of the z signatures of this seed:
-    //      key = sum_k u_k v_k mod 2^61-1, u_k = symbol + 1 <= 256.
-    //      v_k is split into four 16-bit limbs (wave-uniform, scalar); each
-    //      limb sum sum_k u_k * limb is exact in 32 bits for m <= 64
-    //      (64 * 257 * 2^16 < 2^31), one full-rate 24-bit multiply-add per
-    //      limb and sample; the limbs recombine once per key.
     if (!valid) return;
-    for (uint32_t t = 0; t < z; t++) {
-        const uint64_t *vt = v + ((size_t)l * z + t) * m;
-        uint32_t s0 = 0, s1 = 0, s2 = 0, s3 = 0;
-        const uint32_t *pt = pos + (size_t)row * S + t * m;
-        for (uint32_t kk = 0; kk < m; kk++) {
-            const uint32_t u =
-                (uint32_t)(REC ? rec[pt[kk]] : sig[(t * m + kk) * 64 + lane]) + 1u;
-            const uint64_t vv = vt[kk];
-            s0 += __umul24(u, (uint32_t)vv & 0xFFFFu);
-            s1 += __umul24(u, (uint32_t)(vv >> 16) & 0xFFFFu);
-            s2 += __umul24(u, (uint32_t)(vv >> 32) & 0xFFFFu);
-            s3 += __umul24(u, (uint32_t)(vv >> 48));
+    const KeysOut o{keys, sig_out, dk_out, ids_out, dk_shift, n, chunks ? rank : id, rank, id};
+    form_keys<REC>(sig, rec, pos, v, l, row, r, z, m, lane, o);
+}
+
+// Advance tables of pairs of steps, up to 4 letters: Rpair[l][q] holds, for the
+// two letters e = c0 + 4 c1 under and after the pointer at step 2 q, the bits
+// they take (twice the letters passed in the two steps) in bits 4 e .. 4 e + 3.
+__global__ void k_pair_steps(const uint32_t *__restrict__ Rstep, uint64_t pairs,
+                             uint64_t *__restrict__ Rpair) {
+    for (uint64_t q = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; q < pairs;
+         q += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t r0 = Rstep[2 * q], r1 = Rstep[2 * q + 1];
+        uint64_t t = 0;
+        for (uint32_t e = 0; e < 16; e++) {
+            const uint32_t c0 = e & 3u, b0 = (r0 >> c0) & 1u;
+            const uint32_t b1 = (r1 >> (b0 ? e >> 2 : c0)) & 1u;
+            t |= (uint64_t)(2 * (b0 + b1)) << (4 * e);
         }
-        // s0 + s1 2^16 + s2 2^32 + s3 2^48 < 2^80, reduced with 2^61 == 1 (mod P)
-        const unsigned __int128 x = (unsigned __int128)s0 + ((unsigned __int128)s1 << 16) +
-                                    ((unsigned __int128)s2 << 32) + ((unsigned __int128)s3 << 48);
-        uint64_t res = (uint64_t)(x & P61) + (uint64_t)(x >> 61);
-        res = (res & P61) + (res >> 61);
-        if (res >= P61) res -= P61;
-        const uint32_t at = chunks ? rank : id;
-        keys[((size_t)l * z + t) * n + at] = res;
-        if (dk_out) {
-            dk_out[((size_t)l * z + t) * n + rank] = (uint32_t)(res >> dk_shift);
-            ids_out[((size_t)l * z + t) * n + rank] = at;
+        Rpair[q] = t;
+    }
+}
+
+// The walk for alphabets of up to 32 letters and any length: k_embed's mapping
+// (a lane per string, a wave per seed and 64 strings), sampled symbols in LDS.
+//
+// The chain of dependent instructions from one step to the next bounds it.  Up
+// to 4 letters, a table of two steps takes three instructions for both: the
+// low four bits of the window choose an entry, whose low five bits are the
+// shift.  Larger alphabets shift a 64-bit window step by step: a code is the
+// offset of its bit in the step's word as it stands.  What a group of steps
+// reads is fetched ahead: its tables by scalar loads a group before, the next
+// samples' steps, places and step words 64 at a time, one per lane, where the
+// walk of k_embed waits for the scalar cache at every sample.  (Tables in lanes
+// too, read across: 25% slower, for two more instructions a pair.)
+//
+// 60,000 suffixes of 5,000 letters, 6 seeds, 4,800 steps: 650 -> 386 us; length
+// groups up to 36,000 steps: 827 -> 583; 200,001 strings of 25 letters, 5 seeds,
+// 1,101 steps and 320 samples each, six waves per CU by the samples' LDS: 1,331
+// -> 1,072.
+template <int BW>
+__global__ void __launch_bounds__(64)
+    k_walk(const uint32_t *__restrict__ packed, const uint64_t *__restrict__ offsets,
+           uint64_t base, const uint32_t *__restrict__ len, const uint32_t *__restrict__ perm,
+           uint32_t n, const uint32_t *__restrict__ Rstep, uint32_t Lpad,
+           const uint64_t *__restrict__ Rpair, const uint32_t *__restrict__ spos,
+           const uint32_t *__restrict__ sslot, const uint32_t *__restrict__ Jarr,
+           const uint32_t *__restrict__ pos, const uint64_t *__restrict__ v, uint32_t r,
+           uint32_t z, uint32_t m, uint32_t sigma, uint32_t slot_words,
+           uint64_t *__restrict__ keys, uint8_t *__restrict__ sig_out,
+           uint32_t *__restrict__ dk_out, uint32_t *__restrict__ ids_out, uint32_t dk_shift,
+           const uint4 *__restrict__ chunks) {
+    constexpr uint32_t CPD = 32 / BW, LOGBW = BW == 2 ? 1 : (BW == 4 ? 2 : 3);
+    constexpr uint32_t LOGCPD = 5 - LOGBW;
+    constexpr uint32_t G = BW == 8 ? 8 : 16;      // steps per group
+    constexpr uint32_t WORDS = BW == 2 ? 16 : G;  // table words per group
+    extern __shared__ uint32_t lds[];
+    const uint32_t S = z * m;
+    uint8_t *sig = (uint8_t *)lds;                 // [S][64]
+    uint32_t *slots = lds + ((S * 64 + 3) >> 2);   // [64][stride]
+    const uint32_t stride = slot_words + 1;
+    const uint32_t lane = threadIdx.x;
+    const uint32_t chunk = blockIdx.x / r, l = blockIdx.x % r;
+    uint32_t rank = chunk * 64 + lane, row = l;
+    bool valid = rank < n;
+    if (chunks) {
+        const uint4 c = chunks[chunk];
+        rank = c.x + lane;
+        valid = lane < c.y;
+        row = c.z * r + l;
+    }
+    const uint32_t id = valid ? perm[rank] : 0;
+    const uint32_t slen = valid ? len[id] : 0;
+    const uint64_t s0 = valid ? offsets[id] - base : 0;
+    const uint32_t J = Jarr[row];
+    const uint32_t *sp = spos + (size_t)row * S;
+    const uint32_t *ss = sslot + (size_t)row * S;
+    const uint32_t *Rs = Rstep + (size_t)l * Lpad;
+    const uint32_t *tab = BW == 2 ? (const uint32_t *)(Rpair + (size_t)l * (Lpad / 2)) : Rs;
+    uint32_t *myslot = slots + lane * stride;
+    const uint32_t chunk_steps = ((slot_words - 4) << LOGCPD) / G * G;
+
+    // the next 64 samples, one per lane: step, place, and for an odd step of a
+    // pair the step word before it
+    uint32_t k = 0, vpos = 0, vslot = 0, vword = 0, np = 0xFFFFFFFFu;
+    auto fetch_samples = [&]() {
+        const uint32_t q = k + lane;
+        vpos = q < S ? sp[q] : 0xFFFFFFFFu;
+        vslot = q < S ? ss[q] : 0u;
+        vword = BW == 2 && q < S ? Rs[vpos & ~1u] : 0u;
+    };
+    auto next_sample = [&]() {
+        k++;
+        if ((k & 63u) == 0 && k < S) fetch_samples();
+        np = k < S ? readlane_u32(vpos, k & 63u) : 0xFFFFFFFFu;
+    };
+    if (S) {
+        fetch_samples();
+        np = readlane_u32(vpos, 0);
+    }
+    uint32_t i = 0;   // characters consumed by this walk
+    uint32_t ps = 0;  // position of character i inside the staged window
+    uint32_t cur[WORDS];
+#pragma unroll
+    for (uint32_t w = 0; w < WORDS; w++) cur[w] = tab[w];
+
+    for (uint32_t cj = 0; cj < J; cj += chunk_steps) {
+        // ---- stage the next window of every string of the wave into LDS
+        __syncthreads();
+        const bool live = i < slen;
+        if (__builtin_amdgcn_ballot_w64(live) == 0) {
+            // every string is used up: bottom from here on (a walk of three
+            // times the length is, after two thirds of its steps)
+            for (; k < S; k++) sig[ss[k] * 64 + lane] = (uint8_t)sigma;
+            break;
         }
-        if (sig_out) {
-            uint8_t *dst = sig_out + (((size_t)id * r + l) * z + t) * m;
-            for (uint32_t kk = 0; kk < m; kk++)
-                dst[kk] = REC ? rec[pt[kk]] : sig[(t * m + kk) * 64 + lane];
+        const uint64_t gq = (s0 + i) >> LOGCPD;
+        const uint32_t p0 = (uint32_t)((s0 + i) & (CPD - 1));
+        uint32_t nd = 0;
+        if (live) {
+            const uint64_t need = ((uint64_t)p0 + (slen - i) + CPD - 1) / CPD + 1;
+            nd = need < slot_words ? (uint32_t)need : slot_words;
+        }
+        ps = live ? p0 : 0;
+        // every lane copies its own window: independent loads, eight in flight
+        for (uint32_t t0 = 0; t0 < slot_words; t0 += 8) {
+            uint32_t w[8];
+#pragma unroll
+            for (uint32_t u = 0; u < 8; u++) w[u] = (t0 + u < nd) ? packed[gq + t0 + u] : 0u;
+#pragma unroll
+            for (uint32_t u = 0; u < 8; u++)
+                if (t0 + u < nd) myslot[t0 + u] = w[u];
+        }
+        __syncthreads();
+
+        const uint32_t jend = min(J, cj + chunk_steps);
+        for (uint32_t j0 = cj; j0 < jend; j0 += G) {
+            const uint32_t dq = ps >> LOGCPD, sh = (ps & (CPD - 1)) << LOGBW;
+            const uint32_t d0 = myslot[dq], d1 = myslot[dq + 1];
+            uint32_t win = __builtin_amdgcn_alignbit(d1, d0, sh);
+            uint32_t hi = BW == 2 ? 0u : __builtin_amdgcn_alignbit(myslot[dq + 2], d1, sh);
+            __builtin_amdgcn_sched_barrier(0);
+            // the next group's tables (the rows are padded by 64 steps)
+            uint32_t nxt[WORDS];
+            const uint32_t *tn = tab + (size_t)(j0 + G) * WORDS / G;
+#pragma unroll
+            for (uint32_t w = 0; w < WORDS; w++) nxt[w] = tn[w];
+            uint32_t used = 0;  // bits of the window passed
+            if constexpr (BW == 2) {
+#pragma unroll
+                for (uint32_t h = 0; h < 2; h++) {
+                    uint32_t acc = 0;  // its low five bits: bits passed in this half
+                    auto pair = [&](uint32_t q) {
+                        const uint64_t t64 = ((uint64_t)cur[2 * q + 1] << 32) | cur[2 * q];
+                        const uint32_t t = (uint32_t)(t64 >> ((win << 2) & 63u));
+                        acc += t;
+                        win >>= t & 31u;
+                    };
+                    if (np >= j0 + 8 * h + 8) {
+#pragma unroll
+                        for (uint32_t q = 4 * h; q < 4 * h + 4; q++) pair(q);
+                    } else {
+#pragma unroll
+                        for (uint32_t q = 4 * h; q < 4 * h + 4; q++) {
+                            while (np < j0 + 2 * q + 2) {
+                                const uint32_t odd = np & 1u, at = k & 63u;
+                                const uint32_t b = __builtin_amdgcn_ubfe(
+                                    readlane_u32(vword, at), win & 3u, odd);
+                                const uint32_t c = (win >> (2 * b)) & 3u;
+                                const uint32_t x = i + ((used + (acc & 31u)) >> 1) + b;
+                                sig[readlane_u32(vslot, at) * 64 + lane] =
+                                    (uint8_t)(x < slen ? c : sigma);
+                                next_sample();
+                            }
+                            pair(q);
+                        }
+                    }
+                    used += acc & 31u;
+                }
+            } else {
+                auto step = [&](uint32_t s) {
+                    // (codes of 4 bits: the fifth bit is the next letter's, and
+                    // the word's upper half repeats its lower one)
+                    const uint32_t word = BW == 4 ? (cur[s] & 0xFFFFu) * 0x10001u : cur[s];
+                    const uint32_t b = __builtin_amdgcn_ubfe(word, win, 1u) << LOGBW;
+                    used += b;
+                    win = __builtin_amdgcn_alignbit(hi, win, b);
+                    hi >>= b;
+                };
+                if (np >= j0 + G) {
+#pragma unroll
+                    for (uint32_t s = 0; s < G; s++) step(s);
+                } else {
+#pragma unroll
+                    for (uint32_t s = 0; s < G; s++) {
+                        while (np == j0 + s) {
+                            const uint32_t c = win & ((1u << BW) - 1u);
+                            const uint32_t x = i + (used >> LOGBW);
+                            sig[readlane_u32(vslot, k & 63u) * 64 + lane] =
+                                (uint8_t)(x < slen ? c : sigma);
+                            next_sample();
+                        }
+                        step(s);
+                    }
+                }
+            }
+            i += used >> LOGBW;
+            ps += used >> LOGBW;
+#pragma unroll
+            for (uint32_t w = 0; w < WORDS; w++) cur[w] = nxt[w];
         }
     }
+    if (!valid) return;
+    const KeysOut o{keys, sig_out, dk_out, ids_out, dk_shift, n, chunks ? rank : id, rank, id};
+    form_keys<false>(sig, nullptr, pos, v, l, row, r, z, m, lane, o);
 }
 
 // Distortion diagnostic (Section 3.1; normalised Hamming distance under
@@ -937,13 +1167,37 @@ void embed_keys(ej_ctx *ctx, const Prep &pp, const Rand &rd, uint64_t *d_keys, u
             rstep ? launch(k_embed<4, true, true>) : launch(k_embed<4, false, true>);
         else
             rstep ? launch(k_embed<8, true, true>) : launch(k_embed<8, false, true>);
+    } else if (!rstep) {
+        launch(k_embed<8, false, false>);
     } else {
+        uint64_t *pairs = nullptr;
+        if (pp.bw == 2) {
+            const uint64_t np = (uint64_t)rd.r * (rd.Lpad / 2);
+            pairs = ws<uint64_t>(ctx, "walk_pairs", np + 8);
+            hipLaunchKernelGGL(k_pair_steps, dim3(grid_for(ctx, np, 256)), dim3(256), 0,
+                               ctx->stream, (const uint32_t *)rd.d_Rstep, np, pairs);
+            EJ_CHECK_LAUNCH();
+        }
+        auto walk = [&](auto kern) {
+            if (lds > 65536)
+                EJ_HIP(hipFuncSetAttribute((const void *)kern,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            hipLaunchKernelGGL(kern, grid, block, lds, ctx->stream, (const uint32_t *)pp.d_packed,
+                               pp.d_offsets, pp.base, (const uint32_t *)pp.d_len,
+                               (const uint32_t *)pp.d_perm, pp.n, (const uint32_t *)rd.d_Rstep,
+                               rd.Lpad, (const uint64_t *)pairs, (const uint32_t *)rd.d_spos,
+                               (const uint32_t *)rd.d_sslot, (const uint32_t *)rd.d_J,
+                               (const uint32_t *)rd.d_pos, (const uint64_t *)rd.d_v, rd.r, rd.z,
+                               rd.m, rd.sigma, slot_words, d_keys, d_sig, d_dk, d_rank_ids,
+                               dk_shift, d_chunks);
+            EJ_CHECK_LAUNCH();
+        };
         if (pp.bw == 2)
-            rstep ? launch(k_embed<2, true, false>) : launch(k_embed<2, false, false>);
+            walk(k_walk<2>);
         else if (pp.bw == 4)
-            rstep ? launch(k_embed<4, true, false>) : launch(k_embed<4, false, false>);
+            walk(k_walk<4>);
         else
-            rstep ? launch(k_embed<8, true, false>) : launch(k_embed<8, false, false>);
+            walk(k_walk<8>);
     }
 }
 
