@@ -538,7 +538,11 @@ __global__ void __launch_bounds__(64, strip_waves(MAXW, P))
             if (cnt == 0) continue;
             if (SPLIT) {
                 const uint32_t words = class_words(c);
-                KL = lanes;
+                // Up to 2 words stay in one lane however few the pairs are: a
+                // column's chain through two words takes 71 ns, across two
+                // lanes (carry mask, next lane's bit) 80, and 30,000 pairs 90
+                // against 107.  With 3 words it is 92 to 81, so they spread.
+                KL = words <= 2 ? 1 : lanes;
                 while (KL > 1 && KL / 2 >= words) KL /= 2;  // no lane without a word
                 while (KL * MAXW < words) KL *= 2;
             }
@@ -558,7 +562,15 @@ __global__ void __launch_bounds__(64, strip_waves(MAXW, P))
             width = strip_run<N, P, SPLIT>(A, B, pairs, Kq, K, pidx, act, KL, jbeg, jlim,  \
                                            state, SW, meta, dist, colsum);                 \
         break;
-        switch ((words + KL - 1) / KL) {
+#define EJ_STRIP_ONE(N)                                                                    \
+    case 16 + N:                                                                           \
+        if constexpr (SPLIT)                                                               \
+            width = strip_run<N, P, false>(A, B, pairs, Kq, K, pidx, act, KL, jbeg, jlim,  \
+                                           state, SW, meta, dist, colsum);                 \
+        break;
+        switch ((words + KL - 1) / KL + (SPLIT && KL == 1 ? 16 : 0)) {
+            EJ_STRIP_ONE(1)
+            EJ_STRIP_ONE(2)
             EJ_STRIP_CASE(1)
             EJ_STRIP_CASE(2)
             EJ_STRIP_CASE(3)
@@ -577,6 +589,7 @@ __global__ void __launch_bounds__(64, strip_waves(MAXW, P))
             EJ_STRIP_CASE(16)
         }
 #undef EJ_STRIP_CASE
+#undef EJ_STRIP_ONE
         if (ctr_next) strip_append(width, pidx, ctr_next, lists_next, cap);
     }
     if (columns) {
