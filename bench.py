@@ -290,7 +290,7 @@ GRAPH_STATE = {0: "host-sized (sizes read back between stages)",
 
 
 def run_forms(ej, ctx, chars, offs, prm, args, steps=None, warmup=None, tune_reps=2):
-    """The plain per-stage form (default knobs, two-pass verification) and the
+    """The plain per-stage form (default knobs, verification in strips) and the
     batched form (persistent verification replayed from a captured HIP graph,
     knobs from the autotuner), timed on the same device-resident input."""
     steps = args.steps if steps is None else steps
@@ -306,7 +306,8 @@ def run_forms(ej, ctx, chars, offs, prm, args, steps=None, warmup=None, tune_rep
                                 L=prm["L"], flags=fl)
 
     res, ms, stage = time_join(join(flags), steps, warmup)
-    plain = dict(res=res, ms=ms, stage=stage, knobs=ctx.knobs(), kernel="k_verify")
+    plain = dict(res=res, ms=ms, stage=stage, knobs=ctx.knobs(),
+                 kernel=VERIFY_KERNEL[res.verify_form])
     if args.knobs:
         for kv in args.knobs.split(","):
             k, v = kv.split("=")
@@ -638,7 +639,7 @@ def uneven_leg(ej, ctx, oracle, args, peak, col):
     pb = (pw & np.uint64(0xFFFFFFFF)).astype(np.int64)
     long_pw = pw[np.maximum(lens[pa], lens[pb]) > S]
     # the join with the short pass (every short string has thousands of
-    # partners: the form grouped by pattern against the default two-pass form)
+    # partners: the form grouped by pattern against the default strips)
     fl = ej.FLAG_TIMING | ej.FLAG_DEVICE_OUT
 
     def hybrid():
@@ -801,7 +802,8 @@ def plus_leg(ej, ctx, oracle, args, peak, col):
                              tuples=res.n_raw, output_pairs=res.count,
                              verified_pairs_per_s=round(res.n_candidates / (ms / 1e3), 3),
                              stage_ms={k: round(v, 3) for k, v in stage.items()},
-                             roofline=roofline(res, stage, prm, "k_verify", peak))
+                             roofline=roofline(res, stage, prm,
+                                               VERIFY_KERNEL[res.verify_form], peak))
     try:
         ctx.tune_set("verify_mode", 1)
         res_b, ms_b, stage_b = time_join(plus_join(fl | ej.FLAG_GRAPH), args.steps, args.warmup)

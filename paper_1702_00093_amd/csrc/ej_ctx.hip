@@ -120,9 +120,11 @@ void *slab_take(ej_ctx *ctx, size_t bytes, size_t *got) {
 
 void slab_give(ej_ctx *ctx, void *p, size_t bytes) {
     if (!p) return;
+    size_t free_bytes = 0, all_bytes = 0;
+    if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess) (void)hipGetLastError();
     {
         std::lock_guard<std::mutex> hold(ctx->spare_lock);
-        if (bytes <= ctx->spare_max && bytes > ctx->spare_bytes) {
+        if (bytes <= all_bytes / 64 && bytes > ctx->spare_bytes) {
             std::swap(p, ctx->spare);
             ctx->spare_bytes = bytes;
         }
@@ -225,9 +227,6 @@ ej_status ej_create(ej_ctx **out, int device, void *hip_stream) {
         EJ_HIP(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, device));
         ctx->lds_max = lds;
         EJ_HIP(hipHostMalloc((void **)&ctx->pinned, 4096, hipHostMallocDefault));
-        size_t free_bytes = 0, all_bytes = 0;
-        EJ_HIP(hipMemGetInfo(&free_bytes, &all_bytes));
-        ctx->spare_max = all_bytes / 64;
         EJ_HIP(hipMalloc((void **)&ctx->survey, (size_t)ctx->num_cu * SURVEY_BYTES));
         static_scratch_init(device);
         for (int i = 0; i < 8; i++) EJ_HIP(hipEventCreate(&ctx->timers.ev[i]));

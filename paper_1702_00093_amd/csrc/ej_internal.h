@@ -146,7 +146,7 @@ struct ej_ctx {
     // The memory of an index freed last, for the next one (slab_take).
     std::mutex spare_lock;
     void *spare = nullptr;
-    size_t spare_bytes = 0, spare_max = 0;
+    size_t spare_bytes = 0;
     uint8_t *survey = nullptr;   // device, SURVEY_BYTES per CU: a string set's first look
     uint8_t *pinned_out = nullptr;  // grow-only pinned staging of join results
     size_t pinned_out_bytes = 0;
@@ -193,8 +193,8 @@ void sync(ej_ctx *ctx);
 // cached under `key`, which must identify every argument of the launches.
 void run_captured(ej_ctx *ctx, const std::string &key, const std::function<void()> &enqueue);
 // Memory of an index, in one piece.  slab_give keeps the piece in the context
-// when it is within spare_max (a 64th of the device's memory) and larger than
-// the one kept so far, and slab_take hands it out again for a need of at least
+// when it is within a 64th of the device's memory and larger than the one kept
+// so far, and slab_take hands it out again for a need of at least
 // half its size; otherwise they allocate and free.  Allocating and freeing an
 // index in sixteen pieces took from 1.6 ms to 15 ms, depending on what else the
 // process had allocated.  The kept piece is freed with the context, and before
