@@ -139,9 +139,9 @@ __global__ void k_pairs(const uint64_t *__restrict__ key_s, const uint32_t *__re
 
 // Full key and length of the entries that share their top bits with a
 // neighbour in their table; the others are never read by the walk.
-__global__ void k_sorted_attrs_dk(const uint64_t *__restrict__ keys,
-                                  const uint32_t *__restrict__ ids,
+__global__ void k_sorted_attrs_dk(const uint64_t *__restrict__ keys, uint32_t *__restrict__ ids,
                                   const uint32_t *__restrict__ len,
+                                  const uint32_t *__restrict__ perm,
                                   const uint32_t *__restrict__ dk, uint32_t n, uint32_t tot,
                                   uint64_t *__restrict__ key_s, uint32_t *__restrict__ len_s) {
     for (uint64_t e64 = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e64 < tot;
@@ -154,6 +154,7 @@ __global__ void k_sorted_attrs_dk(const uint64_t *__restrict__ keys,
         const uint32_t id = ids[e];
         key_s[e] = keys[(uint64_t)t * n + id];
         len_s[e] = len[id];
+        if (perm) ids[e] = perm[id];
     }
 }
 
@@ -1091,7 +1092,9 @@ void bucket(ej_ctx *ctx, const uint64_t *d_keys, const uint32_t *d_len, const ui
                            ctx->stream, d_keys, d_perm, n, tot, 61u - key_bits, dk, ids0);
         EJ_CHECK_LAUNCH();
     }
-    radix_sort_u32(ctx, dk, ids0, dk2, bk.d_ids, T, n, key_bits, ctx->tune.radix_bits);
+    bk.d_place = inputs_ready ? d_perm : nullptr;
+    radix_sort_u32(ctx, dk, ids0, dk2, bk.d_ids, T, n, key_bits, ctx->tune.radix_bits,
+                   inputs_ready);
     if (!want_groups) {
         bk.d_dk = dk2;
         return;
@@ -1324,7 +1327,7 @@ uint64_t candidates(ej_ctx *ctx, const uint64_t *d_keys, const Buckets &bk, cons
     PairWalk pw{};
     if (by_dk) {
         hipLaunchKernelGGL(k_sorted_attrs_dk, dim3(grid_for(ctx, tot, 256)), dim3(256), 0,
-                           ctx->stream, d_keys, (const uint32_t *)bk.d_ids, d_len,
+                           ctx->stream, d_keys, bk.d_ids, d_len, bk.d_place,
                            (const uint32_t *)bk.d_dk, n, (uint32_t)tot, key_s, len_s);
         EJ_CHECK_LAUNCH();
         pw = pw_buffers(ctx, t, tot);
@@ -1517,7 +1520,7 @@ void candidates_dev(ej_ctx *ctx, const uint64_t *d_keys, const Buckets &bk,
     hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(64), 0, ctx->stream, cnt_dev + 2, 1u);
     EJ_CHECK_LAUNCH();
     hipLaunchKernelGGL(k_sorted_attrs_dk, dim3(grid_for(ctx, tot, 256)), dim3(256), 0, ctx->stream,
-                       d_keys, (const uint32_t *)bk.d_ids, d_len, (const uint32_t *)bk.d_dk, n,
+                       d_keys, bk.d_ids, d_len, bk.d_place, (const uint32_t *)bk.d_dk, n,
                        (uint32_t)tot, key_s, len_s);
     EJ_CHECK_LAUNCH();
     pw_count(ctx, pw, (const uint32_t *)bk.d_dk, (const uint64_t *)key_s, (const uint32_t *)len_s,
@@ -1652,8 +1655,8 @@ uint64_t candidates_plus(ej_ctx *ctx, const uint64_t *d_keys, const Buckets &bk,
     uint32_t *len_s = ws<uint32_t>(ctx, t + "_len_s", tot);
     uint64_t *d_raw = ws<uint64_t>(ctx, t + "_nraw", 1);
     hipLaunchKernelGGL(k_sorted_attrs_dk, dim3(grid_for(ctx, tot, 256)), dim3(256), 0, ctx->stream,
-                       d_keys, (const uint32_t *)bk.d_ids, d_len_entry, (const uint32_t *)bk.d_dk,
-                       ne, (uint32_t)tot, key_s, len_s);
+                       d_keys, bk.d_ids, d_len_entry, bk.d_place, (const uint32_t *)bk.d_dk, ne,
+                       (uint32_t)tot, key_s, len_s);
     EJ_CHECK_LAUNCH();
     const PairWalk pw = pw_buffers(ctx, t, tot);
     pw_count(ctx, pw, (const uint32_t *)bk.d_dk, (const uint64_t *)key_s, (const uint32_t *)len_s,

@@ -458,8 +458,8 @@ __global__ void __launch_bounds__(512)
 struct KeysOut {
     uint64_t *keys;
     uint8_t *sig;
-    uint32_t *dk, *ids;
-    uint32_t dk_shift, n, at, rank, id;
+    uint32_t *dk;
+    uint32_t dk_shift, n, at, id;
 };
 
 template <bool REC>
@@ -489,10 +489,7 @@ __device__ __forceinline__ void form_keys(const uint8_t *sig, const uint8_t *rec
         res = (res & P61) + (res >> 61);
         if (res >= P61) res -= P61;
         o.keys[((size_t)l * z + t) * o.n + o.at] = res;
-        if (o.dk) {
-            o.dk[((size_t)l * z + t) * o.n + o.rank] = (uint32_t)(res >> o.dk_shift);
-            o.ids[((size_t)l * z + t) * o.n + o.rank] = o.at;
-        }
+        if (o.dk) o.dk[((size_t)l * z + t) * o.n + o.at] = (uint32_t)(res >> o.dk_shift);
         if (o.sig) {
             uint8_t *dst = o.sig + (((size_t)o.id * r + l) * z + t) * m;
             for (uint32_t kk = 0; kk < m; kk++)
@@ -518,8 +515,7 @@ __global__ void __launch_bounds__(64)
             const uint32_t *__restrict__ pos, uint32_t Lb, const uint64_t *__restrict__ v,
             uint32_t r, uint32_t z, uint32_t m, uint32_t sigma, uint32_t slot_words,
             uint64_t *__restrict__ keys, uint8_t *__restrict__ sig_out,
-            uint32_t *__restrict__ dk_out, uint32_t *__restrict__ ids_out, uint32_t dk_shift,
-            const uint4 *__restrict__ chunks) {
+            uint32_t *__restrict__ dk_out, uint32_t dk_shift, const uint4 *__restrict__ chunks) {
     constexpr uint32_t CPD = 32 / BW;
     constexpr uint32_t LOGBW = BW == 2 ? 1 : (BW == 4 ? 2 : 3);
     constexpr uint32_t LOGCPD = 5 - LOGBW;
@@ -654,7 +650,7 @@ __global__ void __launch_bounds__(64)
     }
 
     if (!valid) return;
-    const KeysOut o{keys, sig_out, dk_out, ids_out, dk_shift, n, chunks ? rank : id, rank, id};
+    const KeysOut o{keys, sig_out, dk_out, dk_shift, n, dk_out ? rank : id, id};
     form_keys<REC>(sig, rec, pos, v, l, row, r, z, m, lane, o);
 }
 
@@ -703,8 +699,7 @@ __global__ void __launch_bounds__(64)
            const uint32_t *__restrict__ pos, const uint64_t *__restrict__ v, uint32_t r,
            uint32_t z, uint32_t m, uint32_t sigma, uint32_t slot_words,
            uint64_t *__restrict__ keys, uint8_t *__restrict__ sig_out,
-           uint32_t *__restrict__ dk_out, uint32_t *__restrict__ ids_out, uint32_t dk_shift,
-           const uint4 *__restrict__ chunks) {
+           uint32_t *__restrict__ dk_out, uint32_t dk_shift, const uint4 *__restrict__ chunks) {
     constexpr uint32_t CPD = 32 / BW, LOGBW = BW == 2 ? 1 : (BW == 4 ? 2 : 3);
     constexpr uint32_t LOGCPD = 5 - LOGBW;
     constexpr uint32_t G = BW == 8 ? 8 : 16;      // steps per group
@@ -866,7 +861,7 @@ __global__ void __launch_bounds__(64)
         }
     }
     if (!valid) return;
-    const KeysOut o{keys, sig_out, dk_out, ids_out, dk_shift, n, chunks ? rank : id, rank, id};
+    const KeysOut o{keys, sig_out, dk_out, dk_shift, n, dk_out ? rank : id, id};
     form_keys<false>(sig, nullptr, pos, v, l, row, r, z, m, lane, o);
 }
 
@@ -1118,7 +1113,7 @@ void draw_group_samples(ej_ctx *ctx, const ej_params &p, const uint32_t *d_L, ui
 }
 
 void embed_keys(ej_ctx *ctx, const Prep &pp, const Rand &rd, uint64_t *d_keys, uint8_t *d_sig,
-                uint32_t *d_dk, uint32_t *d_rank_ids, uint32_t dk_shift, const uint4 *d_chunks,
+                uint32_t *d_dk, uint32_t dk_shift, const uint4 *d_chunks,
                 uint32_t nchunks) {
     if (pp.n == 0) return;
     const uint32_t S = rd.S;
@@ -1157,7 +1152,7 @@ void embed_keys(ej_ctx *ctx, const Prep &pp, const Rand &rd, uint64_t *d_keys, u
                            (const uint32_t *)rd.d_sslot, (const uint32_t *)rd.d_J,
                            (const uint32_t *)rd.d_pos, Lb, (const uint64_t *)rd.d_v, rd.r, rd.z,
                            rd.m, rd.sigma, slot_words, d_keys,
-                           d_sig, d_dk, d_rank_ids, dk_shift, d_chunks);
+                           d_sig, d_dk, dk_shift, d_chunks);
         EJ_CHECK_LAUNCH();
     };
     if (rec) {
@@ -1188,8 +1183,8 @@ void embed_keys(ej_ctx *ctx, const Prep &pp, const Rand &rd, uint64_t *d_keys, u
                                rd.Lpad, (const uint64_t *)pairs, (const uint32_t *)rd.d_spos,
                                (const uint32_t *)rd.d_sslot, (const uint32_t *)rd.d_J,
                                (const uint32_t *)rd.d_pos, (const uint64_t *)rd.d_v, rd.r, rd.z,
-                               rd.m, rd.sigma, slot_words, d_keys, d_sig, d_dk, d_rank_ids,
-                               dk_shift, d_chunks);
+                               rd.m, rd.sigma, slot_words, d_keys, d_sig, d_dk, dk_shift,
+                               d_chunks);
             EJ_CHECK_LAUNCH();
         };
         if (pp.bw == 2)

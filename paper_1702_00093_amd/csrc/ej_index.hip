@@ -99,19 +99,22 @@ T *own_copy(ej_index *ix, const T *src, size_t count) {
     return dst;
 }
 
+// Attributes of a table's sorted entries; the entries come as length ranks
+// (place[e], keys and lengths by rank) and leave as string positions.
 __global__ void k_sorted_attrs_full(const uint64_t *__restrict__ keys,
-                                    const uint32_t *__restrict__ ids,
-                                    const uint32_t *__restrict__ len, uint32_t n, uint64_t tot,
-                                    uint32_t *__restrict__ dk, uint64_t *__restrict__ key_s,
-                                    uint32_t *__restrict__ len_s) {
+                                    const uint32_t *place, const uint32_t *__restrict__ perm,
+                                    const uint32_t *__restrict__ perm_len, uint32_t n,
+                                    uint64_t tot, uint32_t *ids, uint32_t *__restrict__ dk,
+                                    uint64_t *__restrict__ key_s, uint32_t *__restrict__ len_s) {
     for (uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; e < tot;
          e += (uint64_t)gridDim.x * blockDim.x) {
-        uint64_t t = e / n;
-        uint32_t id = ids[e];
-        uint64_t k = keys[t * n + id];
+        const uint64_t t = e / n;
+        const uint32_t rank = place[e];
+        const uint64_t k = keys[t * n + rank];
         key_s[e] = k;
         dk[e] = (uint32_t)(k >> 29);
-        len_s[e] = len[id];
+        len_s[e] = perm_len[rank];
+        ids[e] = perm[rank];
     }
 }
 
@@ -437,7 +440,7 @@ ej_status ej_index_build(ej_ctx *ctx, const uint8_t *strings, const uint64_t *of
         uint64_t *keys = ws<uint64_t>(ctx, "ix_keys", tot);
         uint32_t *bdk = nullptr, *bids = nullptr;
         bucket_inputs(ctx, tot, "ix", &bdk, &bids);
-        embed_keys(ctx, pp, rd, keys, nullptr, bdk, bids, 61u - 32u);
+        embed_keys(ctx, pp, rd, keys, nullptr, bdk, 61u - 32u);
         Buckets bk;
         bucket(ctx, keys, pp.d_len, pp.d_perm, n, ix->T, 32, bk, "ix", false, true, false);
         // owned copies
@@ -457,15 +460,14 @@ ej_status ej_index_build(ej_ctx *ctx, const uint8_t *strings, const uint64_t *of
         ix->rd.d_sslot = own_copy(ix, rd.d_sslot, (size_t)ix->T * rd.m);
         ix->rd.d_J = own_copy(ix, rd.d_J, (size_t)rd.r);
         ix->d_ids = parts.ids;
-        copy_on(ctx, ix->d_ids, (const uint32_t *)bk.d_ids, tot);
         ix->d_dk = parts.dk;
         ix->d_key_s = parts.key_s;
         ix->d_len_s = parts.len_s;
         if (tot)
             hipLaunchKernelGGL(k_sorted_attrs_full, dim3(grid_for(ctx, tot, 256)), dim3(256), 0,
-                               ctx->stream, (const uint64_t *)keys, (const uint32_t *)ix->d_ids,
-                               (const uint32_t *)pp.d_len, n, tot, ix->d_dk, ix->d_key_s,
-                               ix->d_len_s);
+                               ctx->stream, (const uint64_t *)keys, (const uint32_t *)bk.d_ids,
+                               (const uint32_t *)pp.d_perm, (const uint32_t *)pp.d_perm_len, n,
+                               tot, ix->d_ids, ix->d_dk, ix->d_key_s, ix->d_len_s);
         EJ_CHECK_LAUNCH();
         // what verification needs of the index strings, kept for every query
         // batch: the bit planes (the match masks of the other forms, five
@@ -532,7 +534,7 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         uint64_t *keys = ws<uint64_t>(ctx, "ii_keys", totB);
         uint32_t *bdk = nullptr, *bids = nullptr;
         bucket_inputs(ctx, totB, "ii", &bdk, &bids);
-        embed_keys(ctx, pq, ix->rd, keys, nullptr, bdk, bids, 61u - 32u);
+        embed_keys(ctx, pq, ix->rd, keys, nullptr, bdk, 61u - 32u);
         Buckets bk;
         bucket(ctx, keys, pq.d_len, pq.d_perm, n_new, T, 32, bk, "ii", false, true, false);
         uint32_t *dkB = ws<uint32_t>(ctx, "ii_dkB", totB);
@@ -540,7 +542,8 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         uint32_t *lenB = ws<uint32_t>(ctx, "ii_lenB", totB);
         hipLaunchKernelGGL(k_sorted_attrs_full, dim3(grid_for(ctx, totB, 256)), dim3(256), 0,
                            ctx->stream, (const uint64_t *)keys, (const uint32_t *)bk.d_ids,
-                           (const uint32_t *)pq.d_len, n_new, totB, dkB, keyB, lenB);
+                           (const uint32_t *)pq.d_perm, (const uint32_t *)pq.d_perm_len, n_new,
+                           totB, bk.d_ids, dkB, keyB, lenB);
         EJ_CHECK_LAUNCH();
         hipLaunchKernelGGL(k_add_u32, dim3(grid_for(ctx, totB, 256)), dim3(256), 0, ctx->stream,
                            bk.d_ids, totB, ix->n);

@@ -228,8 +228,9 @@ void scan_exclusive_u64(ej_ctx *ctx, const uint64_t *d_in, uint64_t *d_out, uint
 // arrays may be clobbered.  digit_bits in {4..11}.
 void radix_sort_u32(ej_ctx *ctx, uint32_t *keys_in, uint32_t *vals_in, uint32_t *keys_out,
                     uint32_t *vals_out, uint32_t nseg, uint32_t seglen, uint32_t key_bits,
-                    uint32_t digit_bits);
-// 64-bit keys with 32-bit values, nseg segments of seglen entries sorted each
+                    uint32_t digit_bits, bool positions = false);
+// (positions: the values are the entries' positions in their segments; vals_in
+// is scratch then.)  64-bit keys with 32-bit values, nseg segments of seglen entries sorted each
 void radix_sort_u64_kv(ej_ctx *ctx, uint64_t *keys_in, uint32_t *vals_in, uint64_t *keys_out,
                        uint32_t *vals_out, uint32_t nseg, uint32_t seglen, uint32_t key_bits,
                        uint32_t digit_bits);
@@ -282,16 +283,17 @@ void prepare(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets, uin
              uint32_t fixed_sigma = 0, uint32_t fixed_L = 0, bool need_perm = true);
 void draw_randomness(ej_ctx *ctx, const ej_params &p, uint32_t L, uint32_t sigma, Rand &rd,
                      const char *tag);
-// With d_dk (and d_rank_ids), also the bucketing sort's input: for table t
-// and length rank k, d_dk[t*n + k] = key >> dk_shift of the string of rank k
-// and d_rank_ids[t*n + k] = that string's index.
+// d_keys[t*n + i] = the key of string i in table t; with d_dk, keys go by length
+// rank instead (a wave's strings are neighbours in it: 64 keys in a run, where
+// by index each is a scattered store), and d_dk[t*n + k] = key >> dk_shift of
+// the string of rank k is the bucketing sort's input.
 // With d_chunks, the entries of several groups that share the alphabet and
 // the pi bits and have sample positions of their own (draw_group_samples):
 // nchunks chunks of up to 64 entries of one group each (x = first entry, y =
 // entries, z = group).  pp.n is then the number of entries, pp.d_perm maps an
-// entry to its string, and keys and d_rank_ids are by entry.
+// entry to its string, and keys are by entry (with d_dk).
 void embed_keys(ej_ctx *ctx, const Prep &pp, const Rand &rd, uint64_t *d_keys, uint8_t *d_sig,
-                uint32_t *d_dk = nullptr, uint32_t *d_rank_ids = nullptr, uint32_t dk_shift = 0,
+                uint32_t *d_dk = nullptr, uint32_t dk_shift = 0,
                 const uint4 *d_chunks = nullptr, uint32_t nchunks = 0);
 // Sample positions of ng groups with walk lengths d_L, in place of rd's own
 // (row g * r + l: those draw_randomness draws for walks of d_L[g] steps).
@@ -317,13 +319,18 @@ struct Buckets {
     // [T*n] sorted top key bits: set instead of d_gid/d_gstart when the
     // groups are not built (the pair walk then ends a group where they change)
     uint32_t *d_dk = nullptr;
+    // The strings by length rank, when d_ids holds ranks (the candidate stage
+    // takes lengths by rank then, and puts the strings' indexes in d_ids where
+    // it reads them); null: d_ids holds indexes.
+    const uint32_t *d_place = nullptr;
 };
 // Key bits the bucketing sorts (key_bits 0: the context's knob, then
 // ceil(log2 n) + 6).
 uint32_t bucket_key_bits(ej_ctx *ctx, uint32_t n, uint32_t key_bits);
-// The workspace buffers of bucket()'s sort input (top key bits and string
-// indexes in length order, per table); inputs_ready = the caller filled them
-// (embed_keys with d_dk) and bucket() skips its gather.
+// The workspace buffers of bucket()'s sort input: the top key bits in length
+// order per table, and room for their ranks.  inputs_ready = the caller filled
+// the former (embed_keys with d_dk, so keys go by rank): bucket() skips its
+// gather and leaves ranks in bk.d_ids, with bk.d_place = d_perm.
 void bucket_inputs(ej_ctx *ctx, uint64_t tot, const char *tag, uint32_t **d_dk, uint32_t **d_ids);
 // bk.ngroups is read back to the host only when want_ngroups is set.
 // want_groups = false skips the group ids and starts and leaves the sorted

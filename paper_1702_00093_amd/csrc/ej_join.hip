@@ -545,12 +545,12 @@ bool join_graph(ej_ctx *ctx, const Prep &pp, const Rand &rd, const uint64_t *d_o
         const uint32_t kb = bucket_key_bits(ctx, n, 0);
         uint32_t *bdk = nullptr, *bids = nullptr;
         bucket_inputs(ctx, (uint64_t)T * n, "j", &bdk, &bids);
-        embed_keys(ctx, pp, rd, keys, nullptr, bdk, bids, 61u - kb);
+        embed_keys(ctx, pp, rd, keys, nullptr, bdk, 61u - kb);
         Buckets bk;
         bucket(ctx, keys, pp.d_len, pp.d_perm, n, T, kb, bk, "j", false, true, false);
         uint64_t *pairs = nullptr;
         uint32_t *order = nullptr;
-        candidates_dev(ctx, keys, bk, pp.d_len, p.K, raw_cap, cnt_cap, want_order,
+        candidates_dev(ctx, keys, bk, pp.d_perm_len, p.K, raw_cap, cnt_cap, want_order,
                        caps.sort_dedup || ctx->tune.dedup_sort != 0, cnt_dev, &pairs, &order,
                        "j");
         int32_t *dist = ws<int32_t>(ctx, "j_dist", cnt_cap);
@@ -693,7 +693,7 @@ void join_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets,
     const uint32_t kb = bucket_key_bits(ctx, n, 0);
     uint32_t *bdk = nullptr, *bids = nullptr;
     bucket_inputs(ctx, (uint64_t)T * n, "j", &bdk, &bids);
-    embed_keys(ctx, pp, rd, keys, nullptr, bdk, bids, 61u - kb);
+    embed_keys(ctx, pp, rd, keys, nullptr, bdk, 61u - kb);
     tm.mark();  // 2
     Buckets bk;
     bucket(ctx, keys, pp.d_len, pp.d_perm, n, T, kb, bk, "j", false, true, false);
@@ -706,7 +706,7 @@ void join_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets,
     // what is left of the pairs' bands)
     const bool want_order =
         ctx->tune.verify_mode <= 2 && ctx->tune.verify_order == 1 && !strip_form(ctx);
-    uint64_t cnt = candidates(ctx, keys, bk, pp.d_len, p.K, &pairs, &raw, "j",
+    uint64_t cnt = candidates(ctx, keys, bk, pp.d_perm_len, p.K, &pairs, &raw, "j",
                               want_order && !p.exact_len ? &order : nullptr);
     const uint64_t *cp = pairs;
     cnt = add_short_pairs(ctx, pp, p.K, p.exact_len, pairs, cnt, &cp);
@@ -998,12 +998,12 @@ void join_grouped_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_
         const uint32_t kb = bucket_key_bits(ctx, k, 0);
         uint32_t *bdk = nullptr, *bids = nullptr;
         bucket_inputs(ctx, (uint64_t)NT * k, "g", &bdk, &bids);
-        embed_keys(ctx, pg, rd, keys, nullptr, bdk, bids, 61u - kb);
+        embed_keys(ctx, pg, rd, keys, nullptr, bdk, 61u - kb);
         Buckets bk;
         bucket(ctx, keys, pg.d_len, pg.d_perm, k, NT, kb, bk, "g", false, true, false);
         uint64_t *gp = nullptr;
         uint64_t graw = 0;
-        const uint64_t gc = candidates(ctx, keys, bk, pg.d_len, p.K, &gp, &graw, "g");
+        const uint64_t gc = candidates(ctx, keys, bk, pg.d_perm_len, p.K, &gp, &graw, "g");
         raw += graw;
         append(gp, gc, d_ids);
         sync(ctx);  // the host vectors of this group are reused by the next
@@ -1032,7 +1032,7 @@ void join_grouped_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_
         const uint32_t kb = bucket_key_bits(ctx, entries, 0);
         uint32_t *bdk = nullptr, *bids = nullptr;
         bucket_inputs(ctx, tot, "g", &bdk, &bids);
-        embed_keys(ctx, pe, rd, keys, nullptr, bdk, bids, 61u - kb, d_chunks, nchunks);
+        embed_keys(ctx, pe, rd, keys, nullptr, bdk, 61u - kb, d_chunks, nchunks);
         Buckets bk;
         bucket(ctx, keys, d_len, nullptr, entries, NT, kb, bk, "g", false, true, false);
         uint64_t *gp = nullptr;

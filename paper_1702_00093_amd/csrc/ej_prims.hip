@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(BLK) k_rs_scatter(const K *__restrict__ kin,
         val[rd] = 0;
         if (valid) {
             key[rd] = kin[segbase + t0 + e];
-            if (HAS_VAL) val[rd] = vin[segbase + t0 + e];
+            if (HAS_VAL) val[rd] = vin ? vin[segbase + t0 + e] : t0 + e;
         }
         const uint32_t d = valid ? (uint32_t)(key[rd] >> shift) & mask : 0u;
         dg[rd] = d;
@@ -346,7 +346,7 @@ __global__ void __launch_bounds__(THREADS)
         const uint32_t i = first + r * 64 + lane;
         const bool in = r < (int)turns && i < seglen;
         x[r] = in ? kin[b + i] : (K)0;
-        v[r] = HAS_VAL && in ? vin[b + i] : 0u;
+        v[r] = HAS_VAL && in ? (vin ? vin[b + i] : i) : 0u;
     }
     const uint32_t passes = (key_bits + SEG_BITS - 1) / SEG_BITS;
     uint32_t at = 0;
@@ -421,7 +421,7 @@ __global__ void __launch_bounds__(THREADS)
 
 template <typename K, bool HAS_VAL>
 void radix_sort_impl(ej_ctx *ctx, K *kin, uint32_t *vin, K *kout, uint32_t *vout, uint32_t nseg,
-                     uint32_t seglen, uint32_t key_bits, uint32_t dbits) {
+                     uint32_t seglen, uint32_t key_bits, uint32_t dbits, bool positions = false) {
     uint64_t n = (uint64_t)nseg * seglen;
     if (n == 0) return;
     // Segments that one workgroup sorts: as far as its passes (10 us for 8,192
@@ -429,7 +429,8 @@ void radix_sort_impl(ej_ctx *ctx, K *kin, uint32_t *vin, K *kout, uint32_t *vout
     if (seglen <= (sizeof(K) == 4 ? 8192u : 4096u)) {
         auto launch = [&](auto kern, uint32_t threads) {
             hipLaunchKernelGGL(kern, dim3(nseg), dim3(threads), 0, ctx->stream, (const K *)kin,
-                               (const uint32_t *)vin, kout, vout, seglen, key_bits);
+                               (const uint32_t *)(positions ? nullptr : vin), kout, vout, seglen,
+                               key_bits);
             EJ_CHECK_LAUNCH();
         };
         if (seglen <= 512)
@@ -465,6 +466,7 @@ void radix_sort_impl(ej_ctx *ctx, K *kin, uint32_t *vin, K *kout, uint32_t *vout
     // bits split as evenly as possible: the first key_bits % passes passes
     // take one bit more
     if (passes > 0) dbits = (key_bits + passes - 1) / passes;
+    if (passes == 0 && positions) fail(EJ_EINVAL, "radix sort: positions without key bits");
     if (passes == 0) {
         EJ_HIP(hipMemcpyAsync(kout, kin, n * sizeof(K), hipMemcpyDeviceToDevice, ctx->stream));
         if (HAS_VAL)
@@ -500,7 +502,8 @@ void radix_sort_impl(ej_ctx *ctx, K *kin, uint32_t *vin, K *kout, uint32_t *vout
         scan_exclusive<uint32_t>(ctx, hist, hist, (uint64_t)nseg * (1u << db) * tps, nullptr,
                                  "rs");
         hipLaunchKernelGGL((k_rs_scatter<K, HAS_VAL>), dim3(nseg * tps), dim3(BLK), scat_lds,
-                           ctx->stream, (const K *)a, (const uint32_t *)va, b, vb, seglen, tps,
+                           ctx->stream, (const K *)a,
+                           (const uint32_t *)(positions && p == 0 ? nullptr : va), b, vb, seglen, tps,
                            shift, db, (const uint32_t *)hist);
         EJ_CHECK_LAUNCH();
         shift += db;
@@ -527,10 +530,10 @@ void scan_exclusive_u64(ej_ctx *ctx, const uint64_t *d_in, uint64_t *d_out, uint
 
 void radix_sort_u32(ej_ctx *ctx, uint32_t *keys_in, uint32_t *vals_in, uint32_t *keys_out,
                     uint32_t *vals_out, uint32_t nseg, uint32_t seglen, uint32_t key_bits,
-                    uint32_t digit_bits) {
+                    uint32_t digit_bits, bool positions) {
     if (vals_in)
         radix_sort_impl<uint32_t, true>(ctx, keys_in, vals_in, keys_out, vals_out, nseg, seglen,
-                                        key_bits, digit_bits);
+                                        key_bits, digit_bits, positions);
     else
         radix_sort_impl<uint32_t, false>(ctx, keys_in, nullptr, keys_out, nullptr, nseg, seglen,
                                          key_bits, digit_bits);
