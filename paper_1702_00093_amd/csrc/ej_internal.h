@@ -373,6 +373,10 @@ uint64_t candidates_plus(ej_ctx *ctx, const uint64_t *d_keys, const Buckets &bk,
 // (a << 32) | b into a workspace buffer named after `tag`; returns the count.
 uint64_t unique_sorted_pairs(ej_ctx *ctx, const uint64_t *d_sorted, uint64_t cnt, uint32_t B,
                              uint64_t **d_out, const char *tag);
+// The distinct pairs (a << 32 | b, a < b < n), sorted, of cnt in any order
+// (d_pairs may be clobbered).
+uint64_t unique_pairs(ej_ctx *ctx, uint64_t *d_pairs, uint64_t cnt, uint32_t n,
+                      uint64_t **d_out, const char *tag);
 
 // Match masks of a string set, one bit array per (string, symbol): bit b of
 // word w of string s and symbol c is set iff x_s[32w + b] == c, for

@@ -480,11 +480,8 @@ uint64_t add_short_pairs(ej_ctx *ctx, const Prep &pp, uint32_t K, uint32_t S,
                        (const uint32_t *)pp.d_perm, (const uint64_t *)row, (uint32_t)ns, P,
                        uni + cnt);
     EJ_CHECK_LAUNCH();
-    uint64_t *sorted = ws<uint64_t>(ctx, "sh_sorted", tot);
-    radix_sort_u64(ctx, uni, sorted, tot, 32 + std::max(1u, bits_for(n - 1)),
-                   ctx->tune.radix_bits);
     uint64_t *u = nullptr;
-    const uint64_t c = unique_sorted_pairs(ctx, sorted, tot, 32, &u, "sh");
+    const uint64_t c = unique_pairs(ctx, uni, tot, n, &u, "sh");
     *out = u;
     return c;
 }
@@ -1068,10 +1065,7 @@ void join_grouped_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_
     uint64_t *pairs = nullptr;
     uint64_t cnt = 0;
     if (ucount) {
-        uint64_t *sorted = ws<uint64_t>(ctx, "grp_union_sorted", ucount);
-        radix_sort_u64(ctx, uni, sorted, ucount, 32 + std::max(1u, bits_for(n - 1)),
-                       ctx->tune.radix_bits);
-        cnt = unique_sorted_pairs(ctx, sorted, ucount, 32, &pairs, "grp");
+        cnt = unique_pairs(ctx, uni, ucount, n, &pairs, "grp");
     }
     const uint64_t *cp = pairs;
     cnt = add_short_pairs(ctx, pp, p.K, p.exact_len, pairs, cnt, &cp);

@@ -54,3 +54,18 @@ def test_plus(ctx, oracle_lib, n, T, delta):
     ref = oracle_lib.join_plus(col.chars, col.offsets, 4, 2, 3, 3, delta=delta, T=T, seed=1, L=20)
     print(f"[gpu-case] tuple groups n={n} T={T} raw={ref.n_raw} cand={len(ref.cand)}", flush=True)
     _equal(ctx.join_plus(col.chars, col.offsets, 4, 2, 3, 3, delta=delta, T=T, seed=1, L=20), ref)
+
+
+@pytest.mark.parametrize("n", [2, 3, 1030, 2100])
+def test_union_with_short_pairs(ctx, oracle_lib, n):
+    """The union of the tables' candidates and all short pairs, in groups of up to
+    n codes and by the device-wide sort."""
+    col = _alike(n, 24, 5, n)
+    ref = oracle_lib.join(col.chars, col.offsets, 2, 2, 2, 4, seed=1, L=20, exact_len=24)
+    print(f"[gpu-case] union n={n} cand={len(ref.cand)}", flush=True)
+    for knob in (0, 1):
+        ctx.tune_set("dedup_sort", knob)
+        try:
+            _equal(ctx.join(col.chars, col.offsets, 2, 2, 2, 4, seed=1, L=20, exact_len=24), ref)
+        finally:
+            ctx.tune_set("dedup_sort", 0)
