@@ -22,7 +22,7 @@ using namespace ej;
 struct ej_index {
     ej_ctx *ctx = nullptr;
     ej_params p{};
-    uint32_t n = 0, sigma = 0, L = 0, maxlen = 0, T = 0;
+    uint32_t n = 0, sigma = 0, L = 0, maxlen = 0, minlen = 0, T = 0;
     uint64_t total = 0;            // characters of the indexed strings
     uint8_t lut[256];
     uint64_t hbm_limit = 0;
@@ -432,6 +432,7 @@ ej_status ej_index_build(ej_ctx *ctx, const uint8_t *strings, const uint64_t *of
         ix->sigma = pp.sigma;
         ix->L = pp.L;
         ix->maxlen = pp.maxlen;
+        ix->minlen = pp.minlen;
         ix->total = pp.total;
         memcpy(ix->lut, pp.lut, 256);
         Rand rd;
@@ -622,6 +623,7 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         ix->n = (uint32_t)nN;
         ix->total = charsN;
         ix->maxlen = std::max(ix->maxlen, pq.maxlen);
+        ix->minlen = std::min(ix->minlen, pq.minlen);
     });
     if (slab && st != EJ_OK) (void)hipStreamSynchronize(ctx->stream);
     slab_give(ctx, slab, slab_bytes);  // the replaced one, or this call's on failure
@@ -709,6 +711,15 @@ ej_status ej_query_batch(ej_index *ix, const uint8_t *q, const uint64_t *q_offse
                            counts, first);
         EJ_CHECK_LAUNCH();
         scan_exclusive_u64(ctx, counts, counts, tot, d_raw);
+        // the shortest text of a pair, over the queries that can have one (while
+        // the device counts)
+        uint32_t mintext = ix->maxlen;
+        for (uint32_t i = 0; i < nq; i++) {
+            const uint64_t lq = q_offsets[i + 1] - q_offsets[i];
+            const uint64_t least = std::max<uint64_t>(ix->minlen, lq > Kq[i] ? lq - Kq[i] : 0);
+            if (least <= ix->maxlen && lq + Kq[i] >= ix->minlen)
+                mintext = (uint32_t)std::min<uint64_t>(mintext, std::min(lq, least));
+        }
         uint64_t raw = 0;
         read_back(ctx, d_raw, 8, &raw);
         need += probe_bytes(raw);
@@ -783,8 +794,8 @@ ej_status ej_query_batch(ej_index *ix, const uint8_t *q, const uint64_t *q_offse
             sx.masks = ix->masks;
             sx.planes = ix->d_planes;
             const VerifySet sq = verify_set(pq, dqo, "qm");
-            verify(ctx, ix->sigma, sx, &sq, pairs, cnt, 0, pk, dist, nullptr, nullptr, nullptr, 0,
-                   Kmax);
+            verify(ctx, ix->sigma, sx, &sq, pairs, cnt, 0, pk, dist, nullptr, nullptr, nullptr,
+                   mintext, Kmax);
             uint32_t *flags = ws<uint32_t>(ctx, "q_oflags", cnt);
             uint32_t *pos = ws<uint32_t>(ctx, "q_opos", cnt);
             uint64_t *d_no = ws<uint64_t>(ctx, "q_nout", 1);

@@ -1908,6 +1908,8 @@ void verify(ej_ctx *ctx, uint32_t sigma, VerifySet SA, const VerifySet *setB,
         if (tk.on && tk.nkv < 4) EJ_HIP(hipEventRecord(tk.kv[tk.nkv++], ctx->stream));
     };
     // (word positions in the planes are 32-bit)
+    const uint32_t mtext = std::min(maxlen, maxlen_b);
+    const bool uneven = minlen < mtext / 2;  // the texts' lengths differ
     if (strip_form(ctx) && std::max(plane_words(SA.total), plane_words(SB.total)) < 0x7FFFFF00ull) {
         ctx->last_verify_form = 6;
         auto planes = [&](VerifySet &S) {
@@ -1925,7 +1927,7 @@ void verify(ej_ctx *ctx, uint32_t sigma, VerifySet SA, const VerifySet *setB,
         kmark();
         verify_strips(ctx, sigma, StripSet{SA.planes, SA.off, SA.base, SA.total},
                       StripSet{SB.planes, SB.off, SB.base, SB.total}, d_pairs, count, K, d_Kq,
-                      Kmax, std::min(maxlen, maxlen_b), d_dist, d_columns, d_count);
+                      Kmax, mtext, uneven, d_dist, d_columns, d_count);
         kmark();
         return;
     }
@@ -1946,7 +1948,6 @@ void verify(ej_ctx *ctx, uint32_t sigma, VerifySet SA, const VerifySet *setB,
     const StrSet B{d_codes_b, d_offsets_b, base_b, SB.masks.words, SB.masks.off};
     const uint32_t sig = sigma ? sigma : 1;
     const uint32_t W = 32 * NL;
-    const uint32_t mtext = std::min(maxlen, maxlen_b);
     // full layout: Eq reads reach word (ncols-1)/32 + NL; pattern bits reach
     // ncols + K
     uint32_t wpp_full = (mtext + W + 64) / 32 + 2;
