@@ -95,9 +95,9 @@ __device__ inline void load_planes(const uint32_t *planes, uint32_t words, int32
 __device__ inline void add_mask(uint32_t &a, uint64_t &c) {
     asm("v_addc_co_u32 %0, %1, %0, 0, %1" : "+v"(a), "+s"(c));
 }
-// The value of the next lane in the row of 16 (0 at its end).
+// The value of the next lane (0 in the last).
 __device__ inline uint32_t from_next_lane(uint32_t x) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x101, 0xf, 0xf, true);  // row_shl:1
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x130, 0xf, 0xf, true);  // wave_shl:1
 }
 
 // (a ^ b) | c and a | ~(b | c) in one instruction each.
@@ -132,7 +132,7 @@ __device__ __forceinline__ void match_bits(int w0, const uint32_t (&Y)[P],
 // taken in groups of G and each stage is issued for a whole group before the
 // next one; the scheduling barriers keep the compiler from going back to one
 // word after the other.
-template <int W, int P, bool SPLIT>
+template <int W, int P, bool SPLIT, bool AHEAD>
 __device__ __forceinline__ void strip_column(uint32_t s, const uint32_t (&ty)[P],
                                              const uint32_t (&X)[P][W + 1], uint32_t (&Pv)[W],
                                              uint32_t (&Mv)[W], uint32_t &Z, uint32_t keep,
@@ -206,10 +206,11 @@ __device__ __forceinline__ void strip_column(uint32_t s, const uint32_t (&ty)[P]
         }
     }
     if (SPLIT) {
-        if (P > 2) {
-            // Large alphabets: a lane's words are often all ones (32 rows
-            // without a match), so the carries look ahead across the lanes:
-            // out = carries out, pass = passes a carry on.
+        if (AHEAD) {
+            // Large alphabets, and bands of more than 16 words: a lane's words
+            // are often all ones (32 rows without a match, or rows outside
+            // both strings), so the carries look ahead across the lanes: out =
+            // carries out, pass = passes a carry on.
             uint32_t all = sum[0];
 #pragma unroll
             for (int w = 1; w < W; w++) all &= sum[w];
@@ -250,7 +251,7 @@ __device__ __forceinline__ void strip_column(uint32_t s, const uint32_t (&ty)[P]
 // The strip's columns [jbeg, jlim), W band words per lane and KL lanes per
 // pair.  Returns, in the pair's first lane, the words the
 // pair keeps, or 0 when it is decided.
-template <int W, int P, bool SPLIT>
+template <int W, int P, bool SPLIT, bool AHEAD>
 __device__ __forceinline__ uint32_t strip_run(
     const PlaneSet &A, const PlaneSet &B, const uint64_t *__restrict__ pairs,
     const uint32_t *__restrict__ Kq, uint32_t K, uint32_t pidx, bool act, uint32_t KL,
@@ -364,12 +365,12 @@ __device__ __forceinline__ uint32_t strip_run(
         if (__builtin_amdgcn_ballot_w64(nc < 32u) == 0) {
 #pragma unroll 2
             for (uint32_t s = 0; s < 32; s++)
-                strip_column<W, P, SPLIT>(s, ty, X, Pv, Mv, Z, keep, more);
+                strip_column<W, P, SPLIT, AHEAD>(s, ty, X, Pv, Mv, Z, keep, more);
         } else {
             // a text ends in this block: its lanes stop at its last column
 #pragma unroll 1
             for (uint32_t s = 0; s < 32; s++)
-                if (s < nc) strip_column<W, P, SPLIT>(s, ty, X, Pv, Mv, Z, keep, more);
+                if (s < nc) strip_column<W, P, SPLIT, AHEAD>(s, ty, X, Pv, Mv, Z, keep, more);
         }
         V += nc - Z;
         // keeps the masks below inside the loop (hoisted, they take W registers)
@@ -547,6 +548,12 @@ __global__ void __launch_bounds__(64, strip_waves(MAXW, P))
                 KL = words <= 2 ? 1 : lanes;
                 while (KL > 1 && KL / 2 >= words) KL /= 2;  // no lane without a word
                 while (KL * MAXW < words) KL *= 2;
+                // More than 32 words go over up to 64 lanes while the strip has
+                // less than a wave per SIMD: 400 pairs of 5,000 letters, K =
+                // 2046: 0.89 -> 0.51 ms with 4 letters, 1.06 -> 0.63 with 8 (the
+                // two-pass form, a word in each of 64 lanes: 0.67 and 0.69).
+                if (words > 32 && lanes == 16)
+                    while (KL < 64 && (uint64_t)cnt * KL * 4 <= fill) KL *= 2;
             }
             const uint64_t ng = ((uint64_t)cnt * KL + 63) / 64;
             if (g < g0 + ng) break;
@@ -562,18 +569,36 @@ __global__ void __launch_bounds__(64, strip_waves(MAXW, P))
 #define EJ_STRIP_CASE(N)                                                                   \
     case N:                                                                                \
         if constexpr (N <= MAXW)                                                           \
-            width = strip_run<N, P, SPLIT>(A, B, pairs, Kq, K, pidx, act, KL, jbeg, jlim,  \
-                                           state, SW, meta, dist, colsum);                 \
+            width = strip_run<N, P, SPLIT, (P > 2)>(A, B, pairs, Kq, K, pidx, act, KL,     \
+                                                    jbeg, jlim, state, SW, meta, dist,     \
+                                                    colsum);                               \
+        break;
+// Up to 4 letters, bands over 16 words: the instance that looks ahead (400 pairs
+// of 1,500 letters, K = 700: 298 -> 241 us; of 16 words, K = 500: 221 -> 276).
+#define EJ_STRIP_WIDE(N)                                                                   \
+    case 32 + N:                                                                           \
+        if constexpr (SPLIT && P == 2 && MAXW == 8)                                        \
+            width = strip_run<N, P, SPLIT, true>(A, B, pairs, Kq, K, pidx, act, KL, jbeg,  \
+                                                 jlim, state, SW, meta, dist, colsum);     \
         break;
 #define EJ_STRIP_ONE(N)                                                                    \
     case 16 + N:                                                                           \
         if constexpr (SPLIT)                                                               \
-            width = strip_run<N, P, false>(A, B, pairs, Kq, K, pidx, act, KL, jbeg, jlim,  \
-                                           state, SW, meta, dist, colsum);                 \
+            width = strip_run<N, P, false, false>(A, B, pairs, Kq, K, pidx, act, KL, jbeg, \
+                                                  jlim, state, SW, meta, dist, colsum);    \
         break;
-        switch ((words + KL - 1) / KL + (SPLIT && KL == 1 ? 16 : 0)) {
+        const uint32_t form = !SPLIT ? 0 : KL == 1 ? 16 : P == 2 && words > 16 ? 32 : 0;
+        switch ((words + KL - 1) / KL + form) {
             EJ_STRIP_ONE(1)
             EJ_STRIP_ONE(2)
+            EJ_STRIP_WIDE(1)
+            EJ_STRIP_WIDE(2)
+            EJ_STRIP_WIDE(3)
+            EJ_STRIP_WIDE(4)
+            EJ_STRIP_WIDE(5)
+            EJ_STRIP_WIDE(6)
+            EJ_STRIP_WIDE(7)
+            EJ_STRIP_WIDE(8)
             EJ_STRIP_CASE(1)
             EJ_STRIP_CASE(2)
             EJ_STRIP_CASE(3)
@@ -593,6 +618,7 @@ __global__ void __launch_bounds__(64, strip_waves(MAXW, P))
         }
 #undef EJ_STRIP_CASE
 #undef EJ_STRIP_ONE
+#undef EJ_STRIP_WIDE
         if (ctr_next) strip_append(width, pidx, ctr_next, lists_next, cap);
     }
     if (columns) {
@@ -829,7 +855,9 @@ void verify_strips(ej_ctx *ctx, uint32_t sigma, const StripSet &A, const StripSe
             for (int split = 0; split < 2; split++) {
                 if (!split && n < fill) continue;  // never enough pairs for a lane each
                 if (known && split && n >= fill && NW <= 16) continue;
-                const uint64_t waves = split ? (n * 16 + 63) / 64 + ncls : (n + 63) / 64 + ncls;
+                uint64_t lanes = split ? n * 16 : n;
+                if (split && NW > 32) lanes = std::max(lanes, std::min<uint64_t>(n * 64, fill));
+                const uint64_t waves = (lanes + 63) / 64 + ncls;
                 const uint32_t grid =
                     (uint32_t)std::min<uint64_t>(waves, (uint64_t)ctx->num_cu * 32);
                 hipLaunchKernelGGL(kernel(split), dim3(grid), dim3(64), 0, ctx->stream, SA, SB,
