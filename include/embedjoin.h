@@ -131,7 +131,8 @@ typedef struct {
      * pair with several band words each (2 and 3: "verify_mode" 2), 4 grouped
      * by pattern ("verify_mode" 3), 5 the two-pass form with two or four
      * band words per lane ("verify_wpl" 2 or 4), 6 the strip form (what
-     * "verify_mode" 0 runs with its other knobs at their defaults). */
+     * "verify_mode" 0 runs with its other knobs at their defaults, or 5 where
+     * that is faster). */
     uint32_t verify_form;
     /* 1 when pairs and dist are device pointers (EJ_FLAG_DEVICE_OUT) */
     uint32_t on_device;
@@ -169,8 +170,11 @@ uint64_t ej_workspace_bytes(const ej_ctx *ctx);
  *   "verify_blocks_per_cu"  workgroups per CU of the verification grid (the
  *                           lane form: at most, below the occupancy limit)
  *   "verify_mode"           0: the strip form (a pair's band in one lane's
- *                           registers, or over up to 16 lanes when the pairs
- *                           are few, narrowed after each strip of columns);
+ *                           registers, or over up to 64 lanes when the pairs
+ *                           are few, narrowed after each strip of columns),
+ *                           or the two passes below for the numbers of pairs,
+ *                           band widths and alphabets of up to 32 letters of a
+ *                           join or ej_verify for which they are faster;
  *                           with "verify_wpl", "verify_ring",
  *                           "verify_pass1_cols", "verify_lds_budget",
  *                           "verify_blocks_per_cu" or "verify_len_order" not
