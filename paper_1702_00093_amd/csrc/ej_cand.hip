@@ -792,7 +792,8 @@ __global__ void k_dedup_out(const uint32_t *__restrict__ ucode, const uint32_t *
 // The kept codes go to `out` at the group's place, sorted, ucount[g] of them.
 // A group of more codes than LDS takes is sorted in pieces: its codes are
 // counted by their top 10 bits, and each round takes the bins that fit
-// together.  A bin of more than GS_CAP codes sets *overflow.
+// together.  A bin of more than GS_CAP codes, or a group of more than `most`
+// (see sort_groups), sets *overflow; workgroups that find it set leave.
 //
 // 16 codes per thread, 77 KB of LDS, one workgroup of 16 waves per CU by its
 // registers; bound by its LDS round trips.  36 M codes of 36 bits, 26 M of them
@@ -806,8 +807,9 @@ constexpr uint32_t GS_BINS = 1024;
 
 __global__ void __launch_bounds__(1024)
     k_sort_groups(const uint32_t *__restrict__ codes, const uint32_t *__restrict__ gstart,
-                  uint32_t shift, uint32_t T, uint32_t drop, uint32_t *__restrict__ out,
-                  uint32_t *__restrict__ ucount, uint32_t *__restrict__ overflow) {
+                  uint32_t shift, uint32_t T, uint32_t drop, uint32_t most,
+                  uint32_t *__restrict__ out, uint32_t *__restrict__ ucount,
+                  uint32_t *__restrict__ overflow) {
     extern __shared__ uint32_t buf[];  // [GS_CAP]
     __shared__ uint32_t cnt[GS_WAVES * GS_DIGITS];  // [wave][digit]
     __shared__ uint32_t bins[GS_BINS], wsum[GS_WAVES], taken;
@@ -815,6 +817,16 @@ __global__ void __launch_bounds__(1024)
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const uint32_t b = gstart[g], all_m = gstart[g + 1] - b;
     const uint64_t below = (1ull << lane) - 1ull;
+    if (tid == 0) {
+        if (all_m > most) atomicOr(overflow, 1u);
+        taken = __hip_atomic_load(overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (taken || all_m > most) {
+        if (tid == 0) ucount[g] = 0;
+        return;
+    }
+    __syncthreads();
     // the sum of v over the waves before this one, and over all
     auto waves_before = [&](uint32_t v, uint32_t &total) {
         if (lane == 0) wsum[wave] = v;
@@ -1203,11 +1215,19 @@ bool sort_groups(ej_ctx *ctx, const std::string &t, const CodeGroups &cg, uint64
     uint32_t *uoff = ws<uint32_t>(ctx, t + "_dd_off", cg.NG);
     uint64_t *info = ws<uint64_t>(ctx, t + "_dd_info", 2);  // kept codes, overflow
     EJ_HIP(hipMemsetAsync(info, 0, 16, ctx->stream));
+    // A workgroup alone takes 10 ns a code, and reads its group once a round; the
+    // device-wide sort and the search for distinct codes take 1 ns for 18.  So a
+    // group may hold a 256th of the codes, up to 16 rounds' worth (at the least
+    // one round's).  Near copies in a row fill few groups: with 12,000 of 300,000
+    // strings, one table, 72 M codes lie in groups of up to 1.5 M, and the join
+    // took 70.4 ms with every group sorted here, 10.1 with the device-wide sort.
+    const uint32_t most =
+        (uint32_t)std::max<uint64_t>(GS_CAP, std::min<uint64_t>(16 * GS_CAP, n / 256));
     const size_t lds = 4 * (size_t)GS_CAP;
     EJ_HIP(hipFuncSetAttribute((const void *)k_sort_groups,
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     hipLaunchKernelGGL(k_sort_groups, dim3(cg.NG), dim3(1024), lds, ctx->stream, part,
-                       (const uint32_t *)cg.gstart, cg.shift, T, drop, keep, ucnt,
+                       (const uint32_t *)cg.gstart, cg.shift, T, drop, most, keep, ucnt,
                        (uint32_t *)(info + 1));
     EJ_CHECK_LAUNCH();
     scan_exclusive_u32(ctx, ucnt, uoff, cg.NG, info);
