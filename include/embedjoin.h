@@ -504,7 +504,7 @@ ej_status ej_index_build(ej_ctx *ctx, const uint8_t *strings, const uint64_t *of
  * at build: a byte outside the alphabet is EJ_EALPHABET).  The indexed
  * strings are not embedded again: each table's sorted entries are merged
  * with the new strings' (one binary search per entry), and the strings'
- * codes and match masks are extended.  Later queries answer over the grown
+ * codes and bit planes (match masks) are extended.  Later queries answer over the grown
  * set exactly as an index built from all the strings with that alphabet,
  * truncation and seed.  On failure (EJ_ENOMEM for the grown arrays, which
  * are allocated beside the current ones) the index is unchanged. */
@@ -519,8 +519,9 @@ ej_status ej_index_insert(ej_index *index, const uint8_t *strings, const uint64_
  * each before the memory it counts is requested: with the estimate of
  * ej_query_workspace_estimate, again once the candidate count before
  * de-duplication is known, and again once the de-duplicated count (and so
- * verification's state and the query masks) is known; a refused batch
- * leaves the index usable. */
+ * verification's state, the query masks and, for the first batch under a
+ * verification form that reads them, the index strings' match masks) is known;
+ * a refused batch leaves the index usable. */
 ej_status ej_query_batch(ej_index *index, const uint8_t *q, const uint64_t *q_offsets,
                          uint32_t nq, const uint32_t *Kq, ej_qresult *out);
 /* Bytes of device memory the batch needs before its candidates are known

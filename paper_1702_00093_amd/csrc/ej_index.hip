@@ -379,18 +379,48 @@ uint64_t estimate(const ej_index *ix, uint64_t qbytes, uint32_t nq) {
 uint64_t probe_bytes(uint64_t raw) { return raw * (8 + 8 + 8 + 4 + 4 + 8 + 4); }
 
 // Bytes of verification and output once the de-duplicated count is known:
-// distances, the queries' match masks, the two-pass form's saved state (Pv
-// and Mv of NL band words per pair, rounded up to whole lanes of up to 4
-// words) and its ordering buffers, output flags and positions, result ids
-// and distances.
+// distances, the queries' match masks (their bit planes are at most half of
+// that), the state kept per pair (the larger of the two forms that keep any:
+// the two-pass form's Pv and Mv of NL band words, rounded up to whole lanes of
+// up to 4 words, with its ordering buffers, and the strips'), output flags and
+// positions, result ids and distances.
 uint64_t verify_bytes(const ej_ctx *ctx, uint64_t cnt, uint64_t qbytes, uint32_t nq,
                       uint32_t sigma, uint32_t Kmax) {
     const uint64_t NL = verify_lanes_for(Kmax);
     uint64_t b = cnt * 4;                                           // distances
     b += mask_words_bound(qbytes, nq, sigma) * 4 + 24ull * (nq + 1);  // query masks
-    if (ctx->tune.verify_mode == 0) b += cnt * (8 * (NL + 3) + 4 * 8 + 8);  // two-pass state
+    if (ctx->tune.verify_mode == 0)
+        b += std::max(cnt * (8 * (NL + 3) + 4 * 8 + 8), strip_bytes(cnt, Kmax));
     b += cnt * (4 + 4 + 4 + 4);                                     // output
     return b;
+}
+
+// The match masks of n indexed strings, in one piece: the words, then the
+// offsets.  Only the verification forms other than the strips read them, so
+// they are built when a batch first runs such a form, after its admission has
+// counted them.
+uint64_t mask_offsets_at(uint64_t total, uint64_t n, uint32_t sigma) {
+    return (4 * mask_words_bound(total, (uint32_t)n, sigma) + 255) & ~255ull;
+}
+uint64_t mask_bytes(uint64_t total, uint64_t n, uint32_t sigma) {
+    return mask_offsets_at(total, n, sigma) + 8 * (n + 1);
+}
+
+void index_masks(ej_index *ix) {
+    ej_ctx *ctx = ix->ctx;
+    char *p = own_copy<char>(ix, nullptr, mask_bytes(ix->total, ix->n, ix->sigma));
+    RowMasks rm;
+    try {
+        build_masks(ctx, ix->d_codes, ix->d_offsets, 0, ix->n, ix->total, ix->sigma, rm, "ixm",
+                    (uint32_t *)p, (uint64_t *)(p + mask_offsets_at(ix->total, ix->n, ix->sigma)));
+    } catch (...) {
+        // nothing of a failed build stays with the index
+        (void)hipStreamSynchronize(ctx->stream);
+        ix->owned.pop_back();
+        (void)hipFree(p);
+        throw;
+    }
+    ix->masks = rm;
 }
 
 }  // namespace
@@ -471,8 +501,9 @@ ej_status ej_index_build(ej_ctx *ctx, const uint8_t *strings, const uint64_t *of
                                tot, ix->d_ids, ix->d_dk, ix->d_key_s, ix->d_len_s);
         EJ_CHECK_LAUNCH();
         // what verification needs of the index strings, kept for every query
-        // batch: the bit planes (the match masks of the other forms, five
-        // times their size, follow when a batch first asks for such a form)
+        // batch: the bit planes (the match masks of the other forms, twice
+        // their size for 4 letters and five times for 25, follow when a batch
+        // first asks for such a form)
         ix->d_planes = parts.planes;
         build_planes(ctx, pp.d_codes, pp.total, pp.sigma, ix->d_planes);
         // the owned offsets must be relative to the owned codes: base 0
@@ -570,12 +601,7 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         uint64_t *key = parts.key_s, *offs = parts.offsets;
         uint8_t *codes = parts.codes;
         const bool masked = ix->masks.words != nullptr;  // a batch has asked for them
-        uint32_t *mw = nullptr;
-        uint64_t *mo = nullptr;
-        if (masked) {
-            mw = (uint32_t *)alloc(4 * mask_words_bound(charsN, (uint32_t)nN, ix->sigma));
-            mo = (uint64_t *)alloc(8 * (nN + 1));
-        }
+        char *mp = masked ? (char *)alloc(mask_bytes(charsN, nN, ix->sigma)) : nullptr;
         hipLaunchKernelGGL(k_merge_tables, dim3(grid_for(ctx, totN, 256)), dim3(256), 0,
                            ctx->stream, (const uint32_t *)ix->d_dk, (const uint64_t *)ix->d_key_s,
                            (const uint32_t *)ix->d_len_s, (const uint32_t *)ix->d_ids, ix->n,
@@ -597,16 +623,15 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         EJ_CHECK_LAUNCH();
         RowMasks masks;
         if (masked)
-            build_masks(ctx, codes, offs, 0, (uint32_t)nN, charsN, ix->sigma, masks, "ixm", mw,
-                        mo);
+            build_masks(ctx, codes, offs, 0, (uint32_t)nN, charsN, ix->sigma, masks, "ixm",
+                        (uint32_t *)mp, (uint64_t *)(mp + mask_offsets_at(charsN, nN, ix->sigma)));
         build_planes(ctx, codes, charsN, ix->sigma, planes);
         sync(ctx);
         // swap in the grown arrays; release the replaced ones
-        void *old[] = {(void *)ix->masks.words, (void *)ix->masks.off};
-        for (void *p : old) {
-            auto it = std::find(ix->owned.begin(), ix->owned.end(), p);
-            if (it != ix->owned.end()) ix->owned.erase(it);
-            (void)hipFree(p);
+        if (masked) {
+            void *old = (void *)ix->masks.words;
+            ix->owned.erase(std::find(ix->owned.begin(), ix->owned.end(), old));
+            (void)hipFree(old);
         }
         ix->owned.insert(ix->owned.end(), fresh.begin(), fresh.end());
         fresh.clear();
@@ -767,7 +792,9 @@ ej_status ej_query_batch(ej_index *ix, const uint8_t *q, const uint64_t *q_offse
                 unique_pairs(rb, sorted);
         }
         out->n_candidates = cnt;
+        const bool new_masks = cnt && !strip_form(ctx) && !ix->masks.words;
         need += verify_bytes(ctx, cnt, qtotal, nq, ix->sigma, Kmax);
+        if (new_masks) need += mask_bytes(ix->total, ix->n, ix->sigma);
         admit("with verification");
         out->workspace_bytes = need;
         uint64_t nout = 0;
@@ -784,13 +811,7 @@ ej_status ej_query_batch(ej_index *ix, const uint8_t *q, const uint64_t *q_offse
             sx.total = ix->total;
             sx.maxlen = ix->maxlen;
             sx.tag = "ixm";
-            if (!strip_form(ctx) && !ix->masks.words) {
-                uint32_t *mw = own_copy<uint32_t>(
-                    ix, nullptr, mask_words_bound(ix->total, ix->n, ix->sigma));
-                uint64_t *mo = own_copy<uint64_t>(ix, nullptr, (uint64_t)ix->n + 1);
-                build_masks(ctx, ix->d_codes, ix->d_offsets, 0, ix->n, ix->total, ix->sigma,
-                            ix->masks, "ixm", mw, mo);
-            }
+            if (new_masks) index_masks(ix);
             sx.masks = ix->masks;
             sx.planes = ix->d_planes;
             const VerifySet sq = verify_set(pq, dqo, "qm");

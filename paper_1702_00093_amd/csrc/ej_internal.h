@@ -450,6 +450,8 @@ void verify_strips(ej_ctx *ctx, uint32_t sigma, const StripSet &A, const StripSe
                    const uint64_t *d_pairs, uint64_t count, uint32_t K, const uint32_t *d_Kq,
                    uint32_t Kmax, uint32_t mtext, bool uneven, int32_t *d_dist,
                    unsigned long long *d_columns, const uint64_t *d_count);
+// Bytes verify_strips keeps for `count` pairs (state, lists and order).
+uint64_t strip_bytes(uint64_t count, uint32_t Kmax);
 
 uint32_t verify_lanes_for(uint32_t K);  // lanes per pair, 0 if unsupported
 

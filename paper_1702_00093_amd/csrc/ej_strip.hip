@@ -759,6 +759,16 @@ void build_planes(ej_ctx *ctx, const uint8_t *d_codes, uint64_t total, uint32_t 
         launch(k_planes<8>);
 }
 
+// Pairs per batch: bounds the state and the lists.
+static uint64_t strip_batch(uint64_t count, uint32_t NW) {
+    return std::min<uint64_t>(count, NW <= 16 ? 1u << 24 : 1u << 23);
+}
+
+uint64_t strip_bytes(uint64_t count, uint32_t Kmax) {
+    const uint32_t NW = (Kmax + 33u) / 32u, sets = (width_class(NW) + 1) / 2;
+    return strip_batch(count, NW) * (8ull * NW + 8 + 2 * 4 * sets + 4);
+}
+
 void verify_strips(ej_ctx *ctx, uint32_t sigma, const StripSet &A, const StripSet &B,
                    const uint64_t *d_pairs, uint64_t count, uint32_t K, const uint32_t *d_Kq,
                    uint32_t Kmax, uint32_t mtext, bool uneven, int32_t *d_dist,
@@ -797,8 +807,7 @@ void verify_strips(ej_ctx *ctx, uint32_t sigma, const StripSet &A, const StripSe
     }
     const uint32_t ns = (uint32_t)end.size();
     const uint32_t SW = 2 * NW;
-    // pairs per batch: bounds the state and the lists
-    const uint64_t batch = std::min<uint64_t>(count, NW <= 16 ? 1u << 24 : 1u << 23);
+    const uint64_t batch = strip_batch(count, NW);
     const bool listed = ns > 1 || d_Kq;
     uint32_t *ctr = ws<uint32_t>(ctx, "vs_ctr", (uint64_t)(ns + 1) * CTR);
     uint32_t *state = ns > 1 ? ws<uint32_t>(ctx, "vs_state", batch * SW) : nullptr;
@@ -819,9 +828,11 @@ void verify_strips(ej_ctx *ctx, uint32_t sigma, const StripSet &A, const StripSe
     while (((mtext + 31) / 32 >> sh) > 254) sh++;
     uint32_t *okey = nullptr, *okey2 = nullptr, *oval = nullptr, *order = nullptr;
     if (by_len) {
-        okey = ws<uint32_t>(ctx, "vs_okey", batch);
-        okey2 = ws<uint32_t>(ctx, "vs_okey2", batch);
-        oval = ws<uint32_t>(ctx, "vs_oval", batch);
+        // the sort's scratch is the state, which the first strip writes after it
+        uint32_t *tmp = ns > 1 ? state : ws<uint32_t>(ctx, "vs_state", 2 * batch);
+        okey = tmp;
+        oval = tmp + batch;
+        okey2 = (uint32_t *)(ns > 1 ? meta : ws<uint2>(ctx, "vs_meta", batch));
         order = ws<uint32_t>(ctx, "vs_order", batch);
     }
     auto kernel = [&](bool split) {
