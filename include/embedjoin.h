@@ -534,7 +534,9 @@ uint32_t ej_index_size(const ej_index *index);
 void ej_qresult_free(ej_qresult *res);
 /* The context may keep the memory of one freed index (at most a 64th of the
  * device's) for the next index built or grown on it; it is freed with the
- * context, or when an allocation of the library would fail without it. */
+ * context, or when an allocation of the library would fail without it.  An
+ * index may be freed after its context (and used no more then); nothing is kept
+ * of it. */
 void ej_index_free(ej_index *index);
 
 #ifdef __cplusplus

@@ -256,6 +256,7 @@ void ej_destroy(ej_ctx *ctx) {
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     if (ctx->survey) (void)hipFree(ctx->survey);
     (void)spare_release(ctx);
+    *ctx->alive = false;
     if (ctx->pinned_out) (void)hipHostFree(ctx->pinned_out);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;

@@ -21,6 +21,8 @@ using namespace ej;
 
 struct ej_index {
     ej_ctx *ctx = nullptr;
+    std::shared_ptr<bool> alive;   // whether ctx still exists
+    int device = 0;
     ej_params p{};
     uint32_t n = 0, sigma = 0, L = 0, maxlen = 0, minlen = 0, T = 0;
     uint64_t total = 0;            // characters of the indexed strings
@@ -434,6 +436,8 @@ ej_status ej_index_build(ej_ctx *ctx, const uint8_t *strings, const uint64_t *of
     ej_index *ix = new (std::nothrow) ej_index();
     if (!ix) return EJ_ENOMEM;
     ix->ctx = ctx;
+    ix->alive = ctx->alive;
+    ix->device = ctx->device;
     ej_status st = run_guarded(ctx, [&] {
         if (p->r == 0 || p->z == 0 || p->m == 0 || p->m > 64 || (uint64_t)p->r * p->z > 4096)
             fail(EJ_EINVAL, "invalid r, z, m");
@@ -862,11 +866,14 @@ void ej_qresult_free(ej_qresult *res) {
 
 void ej_index_free(ej_index *ix) {
     if (!ix) return;
-    if (ix->ctx) {
-        (void)hipSetDevice(ix->ctx->device);
+    (void)hipSetDevice(ix->device);
+    if (*ix->alive) {
         (void)hipStreamSynchronize(ix->ctx->stream);
+        slab_give(ix->ctx, ix->slab, ix->slab_bytes);
+    } else if (ix->slab) {
+        // (the context waited for its stream when it was destroyed)
+        (void)hipFree(ix->slab);
     }
-    if (ix->ctx) slab_give(ix->ctx, ix->slab, ix->slab_bytes);
     for (void *p : ix->owned) (void)hipFree(p);
     delete ix;
 }

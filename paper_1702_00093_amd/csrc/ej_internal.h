@@ -8,6 +8,7 @@
 #include <functional>
 #include <new>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -147,6 +148,8 @@ struct ej_ctx {
     std::mutex spare_lock;
     void *spare = nullptr;
     size_t spare_bytes = 0;
+    // whether the context exists, for its indexes, which may outlive it
+    std::shared_ptr<bool> alive = std::make_shared<bool>(true);
     uint8_t *survey = nullptr;   // device, SURVEY_BYTES per CU: a string set's first look
     uint8_t *pinned_out = nullptr;  // grow-only pinned staging of join results
     size_t pinned_out_bytes = 0;
