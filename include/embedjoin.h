@@ -153,7 +153,8 @@ void ej_destroy(ej_ctx *ctx);
 const char *ej_last_error(const ej_ctx *ctx);
 /* Library version as major*10000 + minor*100 + patch. */
 int ej_version(void);
-/* Bytes of device workspace the context currently holds. */
+/* Bytes of device workspace the context currently holds (with the memory it
+ * keeps of a freed index, see ej_index_free). */
 uint64_t ej_workspace_bytes(const ej_ctx *ctx);
 
 /* Launch-shape knobs of the context.  None of them changes any result:
@@ -532,11 +533,12 @@ uint64_t ej_query_workspace_estimate(const ej_index *index, const uint64_t *q_of
 void ej_index_set_hbm_limit(ej_index *index, uint64_t bytes);
 uint32_t ej_index_size(const ej_index *index);
 void ej_qresult_free(ej_qresult *res);
-/* The context may keep the memory of one freed index (at most a 64th of the
- * device's) for the next index built or grown on it; it is freed with the
- * context, or when an allocation of the library would fail without it.  An
- * index may be freed after its context (and used no more then); nothing is kept
- * of it. */
+/* The library may keep the memory of the index freed (or outgrown) last on a
+ * device, at most a 64th of the device's, for the next index built or grown
+ * there.  ej_workspace_bytes counts it in the context that freed that index; it
+ * is freed with that context, by an index of another size, or when an
+ * allocation of the library on the device would fail without it.  An index may
+ * be freed after its context (and used no more then); nothing is kept of it. */
 void ej_index_free(ej_index *index);
 
 #ifdef __cplusplus

@@ -96,18 +96,36 @@ void *ws_get(ej_ctx *ctx, const std::string &name, size_t bytes) {
     return b.p;
 }
 
-void *slab_take(ej_ctx *ctx, size_t bytes, size_t *got) {
-    {
-        std::lock_guard<std::mutex> hold(ctx->spare_lock);
-        if (ctx->spare && ctx->spare_bytes >= bytes && ctx->spare_bytes / 2 <= bytes) {
-            void *p = ctx->spare;
-            *got = ctx->spare_bytes;
-            ctx->spare = nullptr;
-            ctx->spare_bytes = 0;
-            return p;
-        }
-    }
+namespace {
+// The one kept piece of a device, and the context that gave it.
+struct Spare {
+    std::mutex lock;
     void *p = nullptr;
+    size_t bytes = 0;
+    const ej_ctx *owner = nullptr;
+};
+Spare g_spare[MAX_DEVICES];
+
+// Takes the device's piece out (with `owner`: only if that context gave it).
+void *spare_out(int device, const ej_ctx *owner, size_t *bytes) {
+    if (device < 0 || device >= MAX_DEVICES) return nullptr;
+    Spare &s = g_spare[device];
+    std::lock_guard<std::mutex> hold(s.lock);
+    if (owner && s.owner != owner) return nullptr;
+    void *p = s.p;
+    if (bytes) *bytes = s.bytes;
+    s.p = nullptr;
+    s.bytes = 0;
+    s.owner = nullptr;
+    return p;
+}
+}  // namespace
+
+void *slab_take(ej_ctx *ctx, size_t bytes, size_t *got) {
+    void *p = spare_out(ctx->device, nullptr, got);
+    if (p && *got >= bytes && *got / 2 <= bytes) return p;
+    if (p) (void)hipFree(p);  // indexes of another size now
+    p = nullptr;
     hipError_t e = hipMalloc(&p, bytes);
     if (e == hipErrorOutOfMemory && spare_release(ctx)) e = hipMalloc(&p, bytes);
     if (e != hipSuccess) {
@@ -122,24 +140,25 @@ void slab_give(ej_ctx *ctx, void *p, size_t bytes) {
     if (!p) return;
     size_t free_bytes = 0, all_bytes = 0;
     if (hipMemGetInfo(&free_bytes, &all_bytes) != hipSuccess) (void)hipGetLastError();
-    {
-        std::lock_guard<std::mutex> hold(ctx->spare_lock);
-        if (bytes <= all_bytes / 64 && bytes > ctx->spare_bytes) {
-            std::swap(p, ctx->spare);
-            ctx->spare_bytes = bytes;
-        }
+    if (bytes <= all_bytes / 64 && ctx->device < MAX_DEVICES) {
+        Spare &s = g_spare[ctx->device];
+        std::lock_guard<std::mutex> hold(s.lock);
+        std::swap(p, s.p);
+        s.bytes = bytes;
+        s.owner = ctx;
     }
     if (p) (void)hipFree(p);
 }
 
+static uint64_t spare_bytes(const ej_ctx *ctx) {
+    if (ctx->device < 0 || ctx->device >= MAX_DEVICES) return 0;
+    Spare &s = g_spare[ctx->device];
+    std::lock_guard<std::mutex> hold(s.lock);
+    return s.owner == ctx ? s.bytes : 0;
+}
+
 bool spare_release(ej_ctx *ctx) {
-    void *p;
-    {
-        std::lock_guard<std::mutex> hold(ctx->spare_lock);
-        p = ctx->spare;
-        ctx->spare = nullptr;
-        ctx->spare_bytes = 0;
-    }
+    void *p = spare_out(ctx->device, nullptr, nullptr);
     if (p) {
         (void)hipGetLastError();
         (void)hipFree(p);
@@ -255,7 +274,7 @@ void ej_destroy(ej_ctx *ctx) {
     ctx->graphs.clear();
     if (ctx->pinned) (void)hipHostFree(ctx->pinned);
     if (ctx->survey) (void)hipFree(ctx->survey);
-    (void)spare_release(ctx);
+    if (void *p = spare_out(ctx->device, ctx, nullptr)) (void)hipFree(p);
     *ctx->alive = false;
     if (ctx->pinned_out) (void)hipHostFree(ctx->pinned_out);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
@@ -268,7 +287,7 @@ uint64_t ej_workspace_bytes(const ej_ctx *ctx) {
     if (!ctx) return 0;
     uint64_t s = 0;
     for (auto &kv : ctx->ws) s += kv.second.bytes;
-    return s;
+    return s + spare_bytes(ctx);
 }
 
 static uint32_t *tune_slot(ej::Tuning &t, const char *name, uint32_t *lo, uint32_t *hi) {

@@ -9,7 +9,6 @@
 #include <new>
 #include <map>
 #include <memory>
-#include <mutex>
 #include <string>
 #include <vector>
 
@@ -144,10 +143,6 @@ struct ej_ctx {
     int num_cu = 256;
     int lds_max = 65536;         // max dynamic LDS per workgroup
     uint64_t *pinned = nullptr;  // small pinned host buffer for size read-backs
-    // The memory of an index freed last, for the next one (slab_take).
-    std::mutex spare_lock;
-    void *spare = nullptr;
-    size_t spare_bytes = 0;
     // whether the context exists, for its indexes, which may outlive it
     std::shared_ptr<bool> alive = std::make_shared<bool>(true);
     uint8_t *survey = nullptr;   // device, SURVEY_BYTES per CU: a string set's first look
@@ -195,14 +190,14 @@ void sync(ej_ctx *ctx);
 // memset) directly, or, with the context's graph mode on, as a captured graph
 // cached under `key`, which must identify every argument of the launches.
 void run_captured(ej_ctx *ctx, const std::string &key, const std::function<void()> &enqueue);
-// Memory of an index, in one piece.  slab_give keeps the piece in the context
-// when it is within a 64th of the device's memory and larger than the one kept
-// so far, and slab_take hands it out again for a need of at least
-// half its size; otherwise they allocate and free.  Allocating and freeing an
-// index in sixteen pieces took from 1.6 ms to 15 ms, depending on what else the
-// process had allocated.  The kept piece is freed with the context, and before
-// any allocation of the library fails for lack of memory (spare_release).
-// Callers have waited for the work on the piece.
+// Memory of an index, in one piece.  slab_give keeps the piece, the last one
+// given on its device, when it is within a 64th of the device's memory;
+// slab_take hands it out again for a need of at least half its size and frees it
+// otherwise.  Allocating and freeing an index in sixteen pieces took from 1.6 ms
+// to 15 ms, depending on what else the process had allocated.  The kept piece is
+// freed with the context that gave it, and before any allocation of the library
+// on that device fails for lack of memory (spare_release).  Callers have waited
+// for the work on the piece, so any stream may use it next.
 void *slab_take(ej_ctx *ctx, size_t bytes, size_t *got);
 void slab_give(ej_ctx *ctx, void *p, size_t bytes);
 bool spare_release(ej_ctx *ctx);  // whether there was one

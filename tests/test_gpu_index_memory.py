@@ -1,4 +1,6 @@
-"""The memory kept of a freed index is gone with the context that gave it."""
+"""The memory kept of a freed index: counted, of the last index only, one piece
+per device, and gone with the context that gave it."""
+import numpy as np
 import pytest
 
 import synthdata as sd
@@ -22,6 +24,52 @@ def _index(ej, ctx, n):
 
 def _kept(n):
     return 64 * n * 20  # the tables' 20 bytes per string and table
+
+
+def _answers(ej, oracle_lib, ctx, col, ix):
+    q = sd.from_strings([col.string(i) for i in range(5)])
+    Kq = np.full(5, 20, dtype=np.uint32)
+    ref = oracle_lib.query(col.chars, col.offsets, q.chars, q.offsets, Kq, 8, 8, 6, seed=1, L=64)
+    res = ix.query(q.chars, q.offsets, Kq)
+    assert res.ids.tolist() == ref[1].tolist()
+
+
+def test_only_the_last_index_is_kept(ej, oracle_lib):
+    ctx = ej.Context(0)
+    print("[gpu-case] kept index memory", flush=True)
+    _index(ej, ctx, 20000)[1].close()
+    _index(ej, ctx, 20000)[1].close()      # reuses it, and has grown the workspace
+    held = ctx.workspace_bytes
+    col, ix = _index(ej, ctx, 20000)
+    assert ctx.workspace_bytes <= held - _kept(20000)  # in use, not kept
+    _answers(ej, oracle_lib, ctx, col, ix)
+    ix.close()
+    held = ctx.workspace_bytes
+    col, ix = _index(ej, ctx, 500)         # too small for it: the large piece goes
+    assert ctx.workspace_bytes <= held - _kept(20000)
+    _answers(ej, oracle_lib, ctx, col, ix)
+    ix.close()
+    assert ctx.workspace_bytes <= held - _kept(20000) + 2 * _kept(500) + 1000000
+    ctx.close()
+
+
+def test_one_piece_for_two_contexts(ej, oracle_lib):
+    a, b = ej.Context(0), ej.Context(0)
+    print("[gpu-case] kept index memory, two contexts", flush=True)
+    _index(ej, a, 20000)[1].close()
+    _index(ej, b, 20000)[1].close()        # a's piece, given by b now
+    held_a, held_b = a.workspace_bytes, b.workspace_bytes
+    col, ix = _index(ej, a, 20000)
+    assert a.workspace_bytes == held_a     # a kept nothing
+    assert b.workspace_bytes <= held_b - _kept(20000)
+    _answers(ej, oracle_lib, a, col, ix)
+    ix.close()
+    assert a.workspace_bytes >= held_a + _kept(20000)
+    a.close()
+    col, ix = _index(ej, b, 20000)
+    _answers(ej, oracle_lib, b, col, ix)
+    ix.close()
+    b.close()
 
 
 def test_index_freed_after_its_context(ej):
