@@ -299,9 +299,10 @@ void ej_result_free(ej_result *res);
  * repeatedly and descends one launch knob at a time (verification form,
  * first-pass columns, grid, match-mask layout, radix width), keeping in the
  * context the setting with the least wall time (best of `reps` joins per
- * trial).  No knob changes any result.  *best_ms (may be NULL) receives the
- * join time at the chosen setting.  About 15 trials; errors as
- * ej_join_device. */
+ * trial; a setting is kept if it is faster again in a second trial, and all of
+ * them if they are faster together than the settings the call found).  No knob
+ * changes any result.  *best_ms (may be NULL) receives the join time at the
+ * chosen setting.  About 20 to 40 trials; errors as ej_join_device. */
 ej_status ej_autotune(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets, uint32_t n,
                       const ej_params *p, uint32_t reps, float *best_ms);
 

@@ -1226,20 +1226,46 @@ ej_status ej_autotune(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_off
             {&Tuning::bucket_key_bits, {0, 32}, 15},
             {&Tuning::dedup_sort, {0, 1}, 15},
         };
+        const Tuning before = ctx->tune;
         for (const Knob &k : knobs) {
             if (!((k.modes >> ctx->tune.verify_mode) & 1u)) continue;
+            // the strips go by what is left of the pairs' bands
+            if (k.field == &Tuning::verify_order && strip_form(ctx)) continue;
             const uint32_t start = ctx->tune.*(k.field);
             uint32_t best_v = start;
+            double best = cur;
             for (uint32_t v : k.vals) {
                 if (v == start) continue;
                 ctx->tune.*(k.field) = v;
                 const double t = trial_or_inf();
-                if (t < cur) {
-                    cur = t;
+                if (t < best) {
+                    best = t;
                     best_v = v;
                 }
             }
+            ctx->tune.*(k.field) = start;
+            if (best_v == start) continue;
+            // the lowest of several times is low by chance too: once more, both
+            cur = std::min(cur, trial_or_inf());
             ctx->tune.*(k.field) = best_v;
+            const double again = trial_or_inf();
+            if (again < cur)
+                cur = std::min(best, again);
+            else
+                ctx->tune.*(k.field) = start;
+        }
+        // and the whole against the settings it began with, in turn
+        double tuned = 1e300, plain = 1e300;
+        const Tuning after = ctx->tune;
+        for (int i = 0; i < 3 && memcmp(&before, &after, sizeof(Tuning)) != 0; i++) {
+            ctx->tune = before;
+            plain = std::min(plain, trial_or_inf());
+            ctx->tune = after;
+            tuned = std::min(tuned, trial_or_inf());
+        }
+        if (tuned >= plain && plain < 1e300) {
+            ctx->tune = before;
+            cur = plain;
         }
         if (best_ms) *best_ms = (float)cur;
     });
