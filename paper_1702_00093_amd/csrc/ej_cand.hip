@@ -896,6 +896,7 @@ __global__ void __launch_bounds__(1024)
             uint32_t *mine = cnt + wave * GS_DIGITS;
             mine[lane] = 0;
             mine[64 + lane] = 0;
+            lds_order();
             uint32_t rank[GS_ITEMS];
 #pragma unroll
             for (uint32_t r = 0; r < GS_ITEMS; r++) {
@@ -909,12 +910,14 @@ __global__ void __launch_bounds__(1024)
                         const uint64_t bb = __builtin_amdgcn_ballot_w64(bit);
                         peers &= bit ? bb : ~bb;
                     }
-                    // LDS operations of one wave keep their order: a turn's reads
-                    // come before the leaders' updates, those before the next reads
+                    // LDS operations of one wave keep their order (lds_order): a
+                    // turn's reads come before the leaders' updates, those before
+                    // the next reads
                     const uint32_t before = valid ? mine[d] : 0u;
                     rank[r] = before + (uint32_t)__popcll(peers & below);
                     if (valid && (peers & below) == 0)
                         mine[d] = before + (uint32_t)__popcll(peers);
+                    lds_order();
                 }
             }
             __syncthreads();

@@ -52,6 +52,11 @@ __host__ __device__ inline uint64_t stream_key(uint64_t seed, uint32_t tag, uint
     return rng_word(seed, ((uint64_t)tag << 32) | idx);
 }
 
+// LDS operations of one wave take effect in program order; here the compiler
+// keeps that order too, where lanes of a wave read what others wrote without a
+// workgroup barrier between.  No instruction.
+__device__ inline void lds_order() { __atomic_signal_fence(__ATOMIC_SEQ_CST); }
+
 // Lane broadcasts.  The builtin returns a signed int; widen through uint32_t so
 // that 64-bit values (pointers, indices) are not sign-extended.
 __device__ inline uint32_t readlane_u32(uint32_t v, uint32_t lane) {

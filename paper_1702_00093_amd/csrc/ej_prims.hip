@@ -236,25 +236,30 @@ __global__ void __launch_bounds__(BLK) k_rs_scatter(const K *__restrict__ kin,
     for (uint32_t d = threadIdx.x; d < NB; d += BLK)
         base_off[d] = hist[((uint64_t)seg * NB + d) * tps + tile];
     for (uint32_t d = lane; d < NB; d += 64) mycnt[d] = 0;
+    lds_order();
     const uint64_t segbase = (uint64_t)seg * seglen;
     const uint32_t t0 = tile * TILE;
     const uint32_t nvalid = seglen - t0 < (uint32_t)TILE ? seglen - t0 : (uint32_t)TILE;
     // ---- load and rank the wave's elements (LDS reads and writes of one
-    // wave happen in program order: a round's counter reads precede the
-    // leaders' updates, which precede the next round's reads)
+    // wave happen in program order, which the compiler keeps where lds_order
+    // stands: a round's counter reads precede the leaders' updates, which
+    // precede the next round's reads)
     K key[IPT];
     uint32_t val[IPT], dg[IPT], lr[IPT];
     const uint64_t lt_mask = (1ULL << lane) - 1ULL;
 #pragma unroll
     for (int rd = 0; rd < IPT; rd++) {
         const uint32_t e = wave * (64 * IPT) + rd * 64 + lane;
-        const bool valid = e < nvalid;
         key[rd] = 0;
         val[rd] = 0;
-        if (valid) {
+        if (e < nvalid) {
             key[rd] = kin[segbase + t0 + e];
             if (HAS_VAL) val[rd] = vin ? vin[segbase + t0 + e] : t0 + e;
         }
+    }
+#pragma unroll
+    for (int rd = 0; rd < IPT; rd++) {
+        const bool valid = wave * (64 * IPT) + rd * 64 + lane < nvalid;
         const uint32_t d = valid ? (uint32_t)(key[rd] >> shift) & mask : 0u;
         dg[rd] = d;
         uint64_t peers = __builtin_amdgcn_ballot_w64(valid);
@@ -267,6 +272,7 @@ __global__ void __launch_bounds__(BLK) k_rs_scatter(const K *__restrict__ kin,
         const uint32_t before = valid ? mycnt[d] : 0u;
         lr[rd] = before + (uint32_t)__popcll(lower);
         if (valid && lower == 0) mycnt[d] = before + (uint32_t)__popcll(peers);
+        lds_order();
     }
     __syncthreads();
     // ---- digit starts inside the tile, and each wave's first position of
@@ -355,6 +361,7 @@ __global__ void __launch_bounds__(THREADS)
         const uint32_t mask = (1u << bits) - 1u;
         mine[lane] = 0;
         mine[64 + lane] = 0;
+        lds_order();
         uint32_t rank[ITEMS];
 #pragma unroll
         for (int r = 0; r < ITEMS; r++) {
@@ -371,6 +378,7 @@ __global__ void __launch_bounds__(THREADS)
                 const uint32_t before = valid ? mine[d] : 0u;
                 rank[r] = before + (uint32_t)__popcll(peers & below);
                 if (valid && (peers & below) == 0) mine[d] = before + (uint32_t)__popcll(peers);
+                lds_order();
             }
         }
         __syncthreads();
