@@ -451,7 +451,11 @@ __device__ __forceinline__ uint32_t strip_run(
             high += (uint32_t)__shfl_xor((int)high, (int)o, 64);
         }
     if (!has) return 0u;
-    const uint32_t w0 = low, w1 = min(below + high, NW - 1);
+    // A pair's row holds SW / 2 words, those of the largest threshold; the class
+    // it runs in may be wider.  No word past them is kept: the value on a
+    // diagonal is at least its distance from the corner's, so beyond bit Kp the
+    // sum above exceeds Kp.  The bound keeps the row's end in any case.
+    const uint32_t w0 = low, w1 = min(min(below + high, NW - 1), w0 + SW / 2 - 1);
     const uint32_t left = w1 - w0 + 1;
     // the lane of word w0 knows the value on the new bit 0's diagonal
     int32_t v0 = before;
