@@ -262,10 +262,11 @@ __global__ void k_length_keys(const uint32_t *__restrict__ len, uint32_t n,
 
 // Length order of a small set by counting, in one launch: string i's place is
 // the number of strings that are shorter, or as long and before it.  64
-// strings per workgroup, the others split over its 16 waves.  The sort takes
-// two passes of three to five launches, 25 to 50 us whatever the size; this
-// takes 4 us for 2,000 strings and as long as the sort near RANK_MAX.
-constexpr uint32_t RANK_MAX = 8192;
+// strings per workgroup, the others split over its 16 waves.  The sort is two
+// launches (keys, one segment).  One small embedding with it and with this: 58.8
+// and 55.8 us for 64 strings, 65.4 and 63.4 for 2,000, 66.8 and 66.9 for 4,000,
+// 72.8 and 77.7 for 8,192.
+constexpr uint32_t RANK_MAX = 4096;
 
 __global__ void __launch_bounds__(1024)
     k_length_rank(const uint32_t *__restrict__ len, uint32_t n, uint32_t *__restrict__ perm,
