@@ -1854,35 +1854,47 @@ bool strip_form(const ej_ctx *ctx) {
 // weighs more with 5 planes than with 2, and with small alphabets, whose masks
 // are small; they get it back where a pair is one lane's (no lookahead, no
 // idle words), so where the pairs alone fill the chip several times (`fill`
-// lanes are two waves per SIMD), and where they are so few that the chain of
-// one column counts, not its instructions.  Between, the pairs go over 2 to 16
-// lanes that a band of, say, 10 words does not fill.  Both forms timed on
-// similar pairs, 1,500 and 5,000 letters (and a tenth to all of that, `uneven`:
-// the two-pass form's waves of 4 to 32 pairs wait less for their longest
-// text); two-pass over strip times, K = 100 / 300 / 500 / 1000:
+// lanes are two waves per SIMD), where pairs end early or their bands narrow,
+// and where they are so few that the chain of one column counts, not its
+// instructions.  Between, the pairs go over 2 to 16 lanes that a band of, say,
+// 10 words does not fill.  With texts of unlike lengths (`uneven`) the two-pass
+// form's waves of 4 to 32 pairs wait less for their longest.
+//
+// Two-pass over strip times at K = 100 / 300 / 500 / 1000, pairs of 5,000
+// letters 0.6 K edits apart:
 //   4 letters, 15,000 pairs 1.26 / 0.97 / 0.89 / 0.88, 60,000 0.82 / 0.85 /
 //   0.96 / -, 250,000 1.27 / 1.26 / 1.10 / -;
 //   5 letters, 15,000 1.19 / 0.65 / 0.59 / 0.61, 100,000 0.66 / 0.65 / 0.66 /
 //   0.63, 1,200,000 1.06 / 0.96 / 0.93 / -;
 //   20 letters, 30,000 0.96 / 0.65 / 0.83 / 0.79, 100,000 1.12 / 0.87 / 0.85 /
 //   0.72, 400,000 1.62 / 1.18 / 1.09 / -;
-//   25 letters, 100,000 1.41 / 1.12 / 1.05 / 0.85.
-// Unrelated pairs end in the first strip and gain 1.0 to 1.8 everywhere but at
-// K >= 500 on 5 to 20 letters; a join's candidates are mostly related.
+//   25 letters, 15,000 - / - / 0.67 / 0.82, 100,000 1.41 / 1.12 / 1.05 / 0.85.
+// Unrelated pairs end in the first strip: 1.0 to 1.8.  Whole joins of copies
+// further below K lie between (20 letters, K = 200, 150,000 candidates 1.49; of
+// 300 to 6,000 letters 0.94).  The limits stand where neither loses much.
 // More than 32 letters need more rows of masks than LDS holds for many pairs.
-static bool two_pass_pays(const ej_ctx *ctx, uint32_t sigma, uint32_t NW, uint64_t count, bool uneven) {
-    const uint64_t fill = (uint64_t)ctx->num_cu * 512, words = count * NW;
-    if (NW < 3 || sigma > 32 || words <= (sigma > 4 && sigma <= 16 ? fill / 2 : fill)) return false;
-    uint64_t most;  // pairs from which on the strips win, in quarters of fill
-    if (sigma <= 4)
-        most = NW <= 6 ? 3 : NW <= 32 ? (uneven ? 12 : 5) : uneven ? 4 : 0;
-    else if (sigma <= 16)
-        most = NW <= 6 ? (uneven ? 16 : 5) : NW <= 9 ? (uneven ? 24 : 8) : NW <= 16 ? 32 : 64;
-    else if (sigma <= 24)
-        most = NW <= 6 ? 3 : NW <= 13 ? (uneven ? 10 : 5) : NW <= 16 ? (uneven ? 16 : 10) : 64;
-    else
-        most = NW <= 16 ? (uneven ? 6 : 1) : 64;
-    return 4 * count < most * fill;
+static bool two_pass_pays(const ej_ctx *ctx, uint32_t sigma, uint32_t NW, uint64_t count,
+                          bool uneven) {
+    if (NW < 3 || sigma > 32) return false;
+    // from `least` band words and up to `most` pairs, in 16ths of fill
+    uint32_t least = 16, most;
+    if (sigma <= 4) {
+        if (NW < 10) least = 32;
+        most = NW < 7 ? 0 : NW < 10 ? (uneven ? 48 : 12) : NW <= 16 ? (uneven ? 48 : 20)
+             : NW <= 32 ? (uneven ? 48 : 8) : uneven ? 16 : 0;
+    } else if (sigma <= 16) {
+        least = NW < 7 ? 13 : 8;
+        most = NW < 7 ? (uneven ? 64 : 16) : NW < 10 ? (uneven ? 96 : 20)
+             : NW < 14 ? (uneven ? 128 : 64) : NW <= 16 ? 128 : 512;
+    } else if (sigma <= 24) {
+        most = NW < 7 ? 0 : NW < 10 ? (uneven ? 20 : 4) : NW < 14 ? (uneven ? 40 : 16)
+             : NW <= 16 ? (uneven ? 64 : 40) : 256;
+    } else {
+        most = NW < 10 ? 0 : NW < 14 ? (uneven ? 24 : 4) : NW <= 16 ? (uneven ? 24 : 2)
+             : NW <= 32 ? (uneven ? 256 : 2) : 256;
+    }
+    const uint64_t fill = (uint64_t)ctx->num_cu * 512;
+    return 16 * count * NW > least * fill && 16 * count < most * fill;
 }
 
 void build_masks(ej_ctx *ctx, const uint8_t *d_codes, const uint64_t *d_offsets, uint64_t base,

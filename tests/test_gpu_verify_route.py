@@ -21,9 +21,11 @@ def ctx():
 @pytest.mark.parametrize("letters,K,n,form", [
     (b"ACGT", 60, 230, 6),                   # two words: always strips
     (b"ACGT", 100, 200, 6),                  # 4 words x 19,900 pairs: not a lane each
-    (b"ACGT", 200, 220, 5),                  # 7 words x 24,000 pairs
+    (b"ACGT", 200, 220, 6),                  # 7 words x 24,000 pairs
+    (b"ACGT", 200, 290, 5),                  # 7 words x 42,000 pairs
     (b"ACGT", 300, 110, 6),                  # few pairs
-    (b"ACGTN", 100, 200, 5),                 # 5 planes
+    (b"ACGTN", 100, 200, 6),                 # 5 planes, 4 words x 20,000 pairs
+    (b"ACGTN", 100, 245, 5),                 # 4 words x 30,000 pairs
     (b"ACGTN", 100, 120, 6),
     (bytes(range(65, 85)), 300, 220, 5),     # 20 letters
     (bytes(range(65, 90)), 300, 200, 5),     # 25 letters: up to 32,768 pairs
