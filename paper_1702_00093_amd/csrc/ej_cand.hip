@@ -1067,11 +1067,9 @@ uint32_t bucket_key_bits(ej_ctx *ctx, uint32_t n, uint32_t key_bits) {
     return std::min(key_bits, 32u);
 }
 
-void bucket_inputs(ej_ctx *ctx, uint64_t tot, const char *tag, uint32_t **d_dk, uint32_t **d_ids) {
+uint32_t *bucket_input(ej_ctx *ctx, uint64_t tot, const char *tag) {
     if (tot >= 0xFFFFFFFFull) fail(EJ_EUNSUPPORTED, "r*z*n must stay below 2^32");
-    std::string t(tag);
-    *d_dk = ws<uint32_t>(ctx, t + "_dk", tot);
-    *d_ids = ws<uint32_t>(ctx, t + "_ids0", tot);
+    return ws<uint32_t>(ctx, std::string(tag) + "_dk", tot);
 }
 
 void bucket(ej_ctx *ctx, const uint64_t *d_keys, const uint32_t *d_len, const uint32_t *d_perm,
@@ -1099,8 +1097,8 @@ void bucket(ej_ctx *ctx, const uint64_t *d_keys, const uint32_t *d_len, const ui
         sync(ctx);
         return;
     }
-    uint32_t *dk = nullptr, *ids0 = nullptr;
-    bucket_inputs(ctx, tot, tag, &dk, &ids0);
+    uint32_t *dk = bucket_input(ctx, tot, tag);
+    uint32_t *ids0 = ws<uint32_t>(ctx, t + "_ids0", tot);
     uint32_t *dk2 = ws<uint32_t>(ctx, t + "_dk2", tot);
     if (!inputs_ready) {
         hipLaunchKernelGGL(k_bucket_gather, dim3(grid_for(ctx, tot, 256)), dim3(256), 0,

@@ -473,8 +473,7 @@ ej_status ej_index_build(ej_ctx *ctx, const uint8_t *strings, const uint64_t *of
         draw_randomness(ctx, *p, pp.L, pp.sigma, rd, "ix");
         const uint64_t tot = (uint64_t)ix->T * n;
         uint64_t *keys = ws<uint64_t>(ctx, "ix_keys", tot);
-        uint32_t *bdk = nullptr, *bids = nullptr;
-        bucket_inputs(ctx, tot, "ix", &bdk, &bids);
+        uint32_t *bdk = bucket_input(ctx, tot, "ix");
         embed_keys(ctx, pp, rd, keys, nullptr, bdk, 61u - 32u);
         Buckets bk;
         bucket(ctx, keys, pp.d_len, pp.d_perm, n, ix->T, 32, bk, "ix", false, true, false);
@@ -568,8 +567,7 @@ ej_status ej_index_insert(ej_index *ix, const uint8_t *strings, const uint64_t *
         const uint32_t T = ix->T;
         const uint64_t totB = (uint64_t)T * n_new;
         uint64_t *keys = ws<uint64_t>(ctx, "ii_keys", totB);
-        uint32_t *bdk = nullptr, *bids = nullptr;
-        bucket_inputs(ctx, totB, "ii", &bdk, &bids);
+        uint32_t *bdk = bucket_input(ctx, totB, "ii");
         embed_keys(ctx, pq, ix->rd, keys, nullptr, bdk, 61u - 32u);
         Buckets bk;
         bucket(ctx, keys, pq.d_len, pq.d_perm, n_new, T, 32, bk, "ii", false, true, false);

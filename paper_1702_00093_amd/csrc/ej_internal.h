@@ -227,13 +227,13 @@ void scan_exclusive_u64(ej_ctx *ctx, const uint64_t *d_in, uint64_t *d_out, uint
 
 // Stable LSD radix sort of `nseg` independent equal-length segments of
 // `seglen` entries, ordered by bits [0, key_bits) of the keys.  Values
-// (nullable) move with the keys.  Results end in the _out arrays; the _in
-// arrays may be clobbered.  digit_bits in {4..11}.
+// (nullable) move with the keys; with `positions` they are the entries'
+// positions in their segments, and vals_in is scratch.  Results end in the _out
+// arrays; the _in arrays may be clobbered.  digit_bits in {4..11}.
 void radix_sort_u32(ej_ctx *ctx, uint32_t *keys_in, uint32_t *vals_in, uint32_t *keys_out,
                     uint32_t *vals_out, uint32_t nseg, uint32_t seglen, uint32_t key_bits,
                     uint32_t digit_bits, bool positions = false);
-// (positions: the values are the entries' positions in their segments; vals_in
-// is scratch then.)  64-bit keys with 32-bit values, nseg segments of seglen entries sorted each
+// 64-bit keys with 32-bit values, nseg segments of seglen entries sorted each
 void radix_sort_u64_kv(ej_ctx *ctx, uint64_t *keys_in, uint32_t *vals_in, uint64_t *keys_out,
                        uint32_t *vals_out, uint32_t nseg, uint32_t seglen, uint32_t key_bits,
                        uint32_t digit_bits);
@@ -330,11 +330,11 @@ struct Buckets {
 // Key bits the bucketing sorts (key_bits 0: the context's knob, then
 // ceil(log2 n) + 6).
 uint32_t bucket_key_bits(ej_ctx *ctx, uint32_t n, uint32_t key_bits);
-// The workspace buffers of bucket()'s sort input: the top key bits in length
-// order per table, and room for their ranks.  inputs_ready = the caller filled
-// the former (embed_keys with d_dk, so keys go by rank): bucket() skips its
-// gather and leaves ranks in bk.d_ids, with bk.d_place = d_perm.
-void bucket_inputs(ej_ctx *ctx, uint64_t tot, const char *tag, uint32_t **d_dk, uint32_t **d_ids);
+// The workspace buffer of bucket()'s sort input: the top key bits in length
+// order per table.  inputs_ready = the caller filled it (embed_keys with d_dk, so
+// keys go by rank): bucket() skips its gather and leaves ranks in bk.d_ids, with
+// bk.d_place = d_perm.
+uint32_t *bucket_input(ej_ctx *ctx, uint64_t tot, const char *tag);
 // bk.ngroups is read back to the host only when want_ngroups is set.
 // want_groups = false skips the group ids and starts and leaves the sorted
 // top key bits in bk.d_dk (all that candidates() needs).

@@ -540,8 +540,7 @@ bool join_graph(ej_ctx *ctx, const Prep &pp, const Rand &rd, const uint64_t *d_o
     auto enqueue = [&] {
         uint64_t *keys = ws<uint64_t>(ctx, "j_keys", (uint64_t)T * n);
         const uint32_t kb = bucket_key_bits(ctx, n, 0);
-        uint32_t *bdk = nullptr, *bids = nullptr;
-        bucket_inputs(ctx, (uint64_t)T * n, "j", &bdk, &bids);
+        uint32_t *bdk = bucket_input(ctx, (uint64_t)T * n, "j");
         embed_keys(ctx, pp, rd, keys, nullptr, bdk, 61u - kb);
         Buckets bk;
         bucket(ctx, keys, pp.d_len, pp.d_perm, n, T, kb, bk, "j", false, true, false);
@@ -688,8 +687,7 @@ void join_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_offsets,
     // the walk also writes the bucketing sort's input (top key bits and
     // string indexes in length order)
     const uint32_t kb = bucket_key_bits(ctx, n, 0);
-    uint32_t *bdk = nullptr, *bids = nullptr;
-    bucket_inputs(ctx, (uint64_t)T * n, "j", &bdk, &bids);
+    uint32_t *bdk = bucket_input(ctx, (uint64_t)T * n, "j");
     embed_keys(ctx, pp, rd, keys, nullptr, bdk, 61u - kb);
     tm.mark();  // 2
     Buckets bk;
@@ -993,8 +991,7 @@ void join_grouped_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_
         draw_randomness(ctx, p, pg.L, pg.sigma, rd, "g");
         uint64_t *keys = ws<uint64_t>(ctx, "g_keys", (uint64_t)NT * k);
         const uint32_t kb = bucket_key_bits(ctx, k, 0);
-        uint32_t *bdk = nullptr, *bids = nullptr;
-        bucket_inputs(ctx, (uint64_t)NT * k, "g", &bdk, &bids);
+        uint32_t *bdk = bucket_input(ctx, (uint64_t)NT * k, "g");
         embed_keys(ctx, pg, rd, keys, nullptr, bdk, 61u - kb);
         Buckets bk;
         bucket(ctx, keys, pg.d_len, pg.d_perm, k, NT, kb, bk, "g", false, true, false);
@@ -1027,8 +1024,7 @@ void join_grouped_device(ej_ctx *ctx, const uint8_t *d_chars, const uint64_t *d_
         const uint64_t tot = (uint64_t)NT * entries;
         uint64_t *keys = ws<uint64_t>(ctx, "g_keys", tot);
         const uint32_t kb = bucket_key_bits(ctx, entries, 0);
-        uint32_t *bdk = nullptr, *bids = nullptr;
-        bucket_inputs(ctx, tot, "g", &bdk, &bids);
+        uint32_t *bdk = bucket_input(ctx, tot, "g");
         embed_keys(ctx, pe, rd, keys, nullptr, bdk, 61u - kb, d_chunks, nchunks);
         Buckets bk;
         bucket(ctx, keys, d_len, nullptr, entries, NT, kb, bk, "g", false, true, false);

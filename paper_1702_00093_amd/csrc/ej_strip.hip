@@ -493,8 +493,9 @@ __device__ inline void strip_append(uint32_t width, uint32_t pidx, uint32_t *__r
     }
 }
 
-// Waves per SIMD the registers of a kernel with up to `w` band words per lane
-// leave room for.
+// Waves per SIMD asked of a kernel with up to `w` band words per lane: what its
+// column loop leaves room for.  Outside that loop the instances of 2 planes
+// spill (9 to 83 registers up to 8 words, 175 with 16), once a pair and strip.
 constexpr int strip_waves(int w, int P) {
     return P == 2 ? (w <= 4 ? 7 : w <= 8 ? 5 : 4)
          : P == 5 ? (w <= 4 ? 4 : w <= 8 ? 3 : 2)
@@ -503,10 +504,11 @@ constexpr int strip_waves(int w, int P) {
 
 // Bound by VALU instructions (4.0 to 4.7 cycles each per SIMD at four waves:
 // carries, funnel shifts and three-input operations run at half rate).
-// 219,840 pairs of 5,000 letters, K = 500: 3.9 ms in five strips, against 4.2
-// ms for the two-pass form (one band word per lane, 16 lanes per pair, masks
-// from LDS); 25 letters, 50 to 4,000 of them, K = 100, all in one lane: 3.6 ms
-// against 20.4, where that form refilled its mask rows every block of columns.
+// 220,300 pairs of 5,000 letters, K = 500: 3.7 ms in five strips, against 4.2
+// ms for the two-pass form (masks from LDS, a band over several lanes); 26.9 M
+// pairs of 25 letters, 50 to 4,000 of them, K = 100, nearly all in one lane: 5.6
+// ms with their order, against 20.4, where that form refilled its mask rows every
+// block of columns.  Where that form is the faster one: two_pass_pays.
 //
 // One strip over the pairs in the classes' lists (null: all pairs are of one
 // class, the k-th is order[k], or k), the widest class first, 64 / lanes pairs
