@@ -509,13 +509,15 @@ std::string join_shape(ej_ctx *ctx, const Prep &pp, const uint8_t *d_chars,
     char key[512];
     snprintf(key, sizeof(key),
              "join %p %p %u %llu %llu %u %u %u %u %u %u %u %llu | %u %u %u %u %u %u %u %u %u %u "
-             "%u %u %u %u",
+             "%u %u %u %u | %d",
              (const void *)d_chars, (const void *)d_offsets, pp.n, (unsigned long long)pp.base,
              (unsigned long long)pp.total, pp.sigma, pp.maxlen, pp.L, p.K, p.r, p.z, p.m,
              (unsigned long long)p.seed, t.verify_mode, t.verify_order, t.verify_split,
              t.verify_pass1_cols, t.verify_blocks_per_cu, t.verify_ring, t.verify_lds_budget,
              t.embed_lds_budget, t.radix_bits, t.bucket_key_bits, t.dedup_sort, t.raw_limit,
-             t.verify_wpl, t.verify_len_order);
+             t.verify_wpl, t.verify_len_order,
+             // (verify()'s form, order and buffers go by this)
+             (int)(pp.minlen < pp.maxlen / 2));
     return key;
 }
 
